@@ -19,7 +19,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libqcoll.so")
 
 HOST_SOURCES = ["plan.cpp", "api.cpp", "transport.cpp"]
-DEVICE_SOURCES = ["kernels_2d.hip", "kernels_2d16.hip", "kernels_2d64.hip", "kernels_multi.hip", "kernels_3d.hip",
+DEVICE_SOURCES = ["kernels_fft.hip", "kernels_2d.hip", "kernels_2d16.hip", "kernels_2d64.hip", "kernels_multi.hip", "kernels_3d.hip",
                   "kernels_galerkin.hip", "kernels_transport.hip", "kernels_classical.hip", "noalloc.hip"]
 ARCH = "gfx950"
 
@@ -31,7 +31,10 @@ DEVICE_FLAGS = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang
 # Per-file additions: the 32x32 kernels are scheduled for instruction-level
 # parallelism (3% shorter eval launches at the same register count and bitwise
 # equal results; the 64-point kernels were 1.5% slower with it).
-FILE_FLAGS = {"kernels_2d.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+# The batched kernel reads its slot table in place: with more reads of it than
+# the compiler's default limit (300) the table is copied to each lane's scratch.
+FILE_FLAGS = {"kernels_2d.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+              "kernels_multi.hip": ["-mllvm", "-instcombine-max-copied-from-constant-users=100000"]}
 
 
 def _hipcc() -> str:

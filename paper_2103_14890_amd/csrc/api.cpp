@@ -45,7 +45,8 @@ struct qcoll_plan_s {
   int64_t scratch_stride = 0;
   int64_t scratch_blocks = 0;
   int tile = 32;
-  // 2D plans with N <= 16 also hold the tables of the 32x32 tile kernels (zero
+  bool fft = false;   // runs on the FP64 FFT kernels: one table (filt) for every tile family
+  // 2D plans on the matrix kernels with N <= 16 also hold the tables of the 32x32 tile kernels (zero
   // padded), so that the autotuner can choose the tile family: alt_* is the set
   // of the tile that is not selected, swapped with the fields above by set_tile.
   int alt_tile = 0;
@@ -322,9 +323,11 @@ int build_device_2d16(qcoll_plan_s* p) {
   return QCOLL_OK;
 }
 
-// Exchange the selected tile's tables with the alternate set (2D, N <= 16).
+// Exchange the selected tile's tables with the alternate set (2D, N <= 16; the
+// FFT kernels have one table for both families).
 void swap_tile_tables(qcoll_plan_s* p) {
   std::swap(p->tile, p->alt_tile);
+  if (p->fft) return;
   std::swap(p->econst, p->alt_econst);
   std::swap(p->filt, p->alt_filt);
   std::swap(p->filt_exp, p->alt_filt_exp);
@@ -333,8 +336,41 @@ void swap_tile_tables(qcoll_plan_s* p) {
 }
 
 int launch(const qcoll::KernelArgs& a, hipStream_t stream) {
+  if (a.fft) return qcoll::launch_fft(a, stream);
   if (a.tile == 64) return qcoll::launch_2d64(a, stream);
   return a.tile == 32 ? qcoll::launch_2d32(a, stream) : qcoll::launch_2d16(a, stream);
+}
+
+// Plans that run on the FP64 FFT kernels: FX16 without the projection, up to 32
+// points per axis. Measured against the split-FP16 matrix kernels (4096 cells, M =
+// 8, hard spheres, float Q): 20 points 195 -> 80 us, 24 points 201 -> 99, 32 points
+// 216 -> 145; 10000 cells of 16 points 101 -> 73 (Maxwell, M = 16: 48.6 -> 45.5).
+// Plans with the projection stay on the matrix kernels: their double Q carries the
+// digits of that arithmetic below 1e-6, and callers compare it with earlier
+// results at double precision. So do the fine grids of Galerkin plans.
+bool fft_supported(const qcoll_plan_s* p) {
+  return p->hp.d == 2 && p->precision == QCOLL_MIX_FX16 && !(p->flags & QCOLL_CONSERVE) && !p->galerkin &&
+         p->hp.N <= 32;
+}
+
+// Filter table of the FFT kernels. Entry q < P is the packed multiplier of gain
+// transform q, entry P the loss multiplier. The multipliers are even,
+// m(-k) = m(k), so half of the rows are held: [q][k2][k1 = 0 .. N/2], complex.
+int build_device_fft(qcoll_plan_s* p) {
+  const auto& hp = p->hp;
+  const int n = hp.N, P = static_cast<int>(hp.packed.size());
+  const int H = n / 2 + 1;
+  std::vector<double> ft(static_cast<size_t>(P + 1) * n * H * 2);
+  size_t o = 0;
+  for (int q = 0; q <= P; ++q)
+    for (int k2 = 0; k2 < n; ++k2)
+      for (int k1 = 0; k1 < H; ++k1) {
+        const int64_t k = static_cast<int64_t>(k1) * n + k2;
+        const std::complex<double> m = q < P ? hp.packed[q][k] : std::complex<double>(hp.loss_scaled[k], 0.0);
+        ft[o++] = m.real();
+        ft[o++] = m.imag();
+      }
+  return upload(ft, &p->filt, p->device_bytes);
 }
 
 // Device tables of the tile-64 kernel (grids n = 2 n', n' <= 32): n'-point
@@ -575,6 +611,7 @@ qcoll::KernelArgs make_args(const qcoll_plan_s* p) {
   a.max_blocks = p->max_blocks;
   a.waves_per_block = p->waves_per_block;
   a.tile = p->tile;
+  a.fft = p->fft ? 1 : 0;
   a.tw = p->tw;
   a.precision = p->precision;
   a.split = p->split;
@@ -710,6 +747,10 @@ static int plan_create(qcoll_plan_t* out, int d, int n_per_dim, double L, int ke
       if (!(rc = upload(bt, &p->cl_betaT, p->device_bytes))) rc = upload(tw, &p->cl_tw, p->device_bytes);
     } else if (p->hp.d == 3) {
       rc = build_device_3d(p);
+    } else if (fft_supported(p)) {
+      p->fft = true;
+      if (p->tile == 16) p->alt_tile = 32;
+      rc = build_device_fft(p);
     } else {
       rc = p->tile == 64 ? build_device_2d64(p) : (p->tile == 32 ? build_device_2d32(p) : build_device_2d16(p));
       if (!rc && p->tile == 16) {   // the 32x32 tile family as the alternate set
@@ -1250,8 +1291,9 @@ int qcoll_step_multi(const qcoll_plan_t* plans, int nplans, float* const* f, con
 
 static bool split_ok(const qcoll_plan_s* p, int split);
 
-// Eight wavefronts per workgroup select the ping-pong variant of the FX16
-// 32x32 kernel (two wavefronts per SIMD in alternating matrix/vector phases).
+// Eight cells per workgroup: FX16 plans of the 32-point family (on the matrix
+// kernels the ping-pong variant, two wavefronts per SIMD in alternating
+// matrix/vector phases).
 static bool pingpong_ok(const qcoll_plan_s* p) {
   return p->on_device && p->hp.d == 2 && p->tile == 32 && p->precision == QCOLL_MIX_FX16 && !p->classical;
 }

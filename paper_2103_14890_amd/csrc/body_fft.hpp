@@ -1,0 +1,332 @@
+// Per-cell body of the 2D FX16 plans on grids of up to 32 points per axis: one
+// wavefront per cell, FP64 FFTs in registers. Shared by the single-plan and the
+// batched kernels.
+//
+// Dataflow (section 3.3): forward DFT of f -> f_hat; for every packed filter
+// m_q the inverse DFT of m_q f_hat, whose real and imaginary parts are the two
+// real fields g and h of a pair of directions (their product is the gain
+// contribution); the inverse DFT of l f_hat is the loss field; Q = gain - f L.
+//
+// A lane holds one whole line of a transform (N complex values), so that both
+// 1-D passes of a transform are register FFTs and one transposition through LDS
+// between them is the only exchange. A line needs G = 16 or 32 lanes' worth of
+// lines, so a wavefront runs T = 64 / G transforms at a time, transform slot t on
+// lanes t G .. t G + G - 1; the slots' gain sums are added once per cell.
+//
+// The filters are real-even pairs, m(-k) = m(k), and f_hat(-k) is the conjugate
+// of f_hat(k): a lane of a row k1 < 0 computes the conjugate of its row from the
+// entries of row -k1 (with conj m), and the reader of the transposition takes
+// conjugates of those rows (a sign folded into the second pass). So the filter
+// table and the spectrum hold half of the rows.
+//
+// What bounds it: FP64 vector issue. Per pair of 32-point transforms a lane issues
+// 990 FP64 instructions (2 x 418 FFT, 124 filter, 32 gain), 64 lane swaps and 31
+// sign flips, against about 1660 vector instructions and 192 MFMAs of the
+// split-FP16 matrix form. 4096 cells of 32 x 32 (hard spheres, M = 8) take 57.7 M
+// wavefront instructions, 124-135 us at the 2.2-2.4 ns per instruction that two
+// wavefronts on a SIMD reach; measured 145 us, the matrix form 216 us.
+#pragma once
+
+#include "fft_reg.hpp"
+#include "kernels_common.hpp"
+
+namespace qcoll {
+namespace {
+
+// Swap the odd 16-lane rows (the upper 32 lanes) of a with the even rows (the
+// lower 32 lanes) of b.
+__device__ __forceinline__ void swap16(double& a, double& b) {
+  const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(x), static_cast<unsigned>(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(x >> 32), static_cast<unsigned>(y >> 32),
+                                                   false, false);
+  a = __hiloint2double(static_cast<int>(hi[0]), static_cast<int>(lo[0]));
+  b = __hiloint2double(static_cast<int>(hi[1]), static_cast<int>(lo[1]));
+}
+__device__ __forceinline__ void swap32(double& a, double& b) {
+  const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(x), static_cast<unsigned>(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(x >> 32), static_cast<unsigned>(y >> 32),
+                                                   false, false);
+  a = __hiloint2double(static_cast<int>(hi[0]), static_cast<int>(lo[0]));
+  b = __hiloint2double(static_cast<int>(hi[1]), static_cast<int>(lo[1]));
+}
+
+// Flip the sign of x where `mask` has the sign bit.
+__device__ __forceinline__ double flip(double x, int mask) {
+  return __hiloint2double(__double2hiint(x) ^ mask, __double2loint(x));
+}
+
+template <int NN>
+struct FftGrid {
+  static constexpr int G = NN > 16 ? 32 : 16;        // lanes per transform
+  static constexpr int T = 64 / G;                   // transforms at a time
+  static constexpr int H = NN / 2 + 1;               // rows kept of the spectrum and the filters (k1 = 0 .. N/2)
+  // The transposition goes through LDS one real component at a time; above 28
+  // points also 16 registers at a time (a 2 x 2 block swap between registers
+  // and lanes first), so that eight wavefronts fit a CU's 160 KB.
+  static constexpr bool CHUNK = NN > 28;
+  static constexpr int XS = CHUNK ? 65 : T * NN + 1; // odd: the column reads fall on distinct banks
+  static constexpr int XD = (CHUNK ? 16 : NN) * XS;
+  // the layout of the epilogue: slot t holds rows t V .. t V + V - 1 of its column
+  static constexpr int N = G, V = (NN + T - 1) / T;
+  __device__ static int row(int v, int lane) { return V * (lane / G) + v; }
+  __device__ static int col(int lane) { return lane & (G - 1); }
+  static constexpr int kFh = 2 * NN * H;             // doubles
+  static constexpr int kWaveBytes = ((kFh + (XD > V * 64 ? XD : V * 64)) * 8 + 15) / 16 * 16;
+};
+
+// Transpose within each transform slot: lane r holds line r, register v its
+// point v; afterwards lane c holds point c of every line, register = line.
+template <int NN>
+__device__ __forceinline__ void transpose(double (&x)[NN], double* buf, int lane) {
+  using F = FftGrid<NN>;
+  const int t = lane / F::G, r = lane & (F::G - 1);
+  if constexpr (F::CHUNK) {
+    double y[32];
+#pragma unroll
+    for (int v = 0; v < 32; ++v) y[v] = v < NN ? x[v] : 0.0;
+    // 2 x 2 blocks: afterwards lane (t, rb, r0), register (c1, c0) holds line
+    // 16 c1 + r0, point 16 rb + c0
+#pragma unroll
+    for (int v = 0; v < 16; ++v) swap16(y[v], y[v + 16]);
+    const int rd = (r & 15) * F::XS + 32 * t + (r & 16);
+#pragma unroll
+    for (int c1 = 0; c1 < 2; ++c1) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) buf[v * F::XS + lane] = y[16 * c1 + v];
+      lds_fence();
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (16 * c1 + j < NN) x[16 * c1 + j] = buf[rd + j];
+      lds_fence();
+    }
+  } else {
+    const int wr = r < NN ? t * NN + r : F::T * NN;
+    const int rd = (r < NN ? r : 0) * F::XS + t * NN;
+#pragma unroll
+    for (int v = 0; v < NN; ++v) buf[v * F::XS + wr] = x[v];
+    lds_fence();
+#pragma unroll
+    for (int j = 0; j < NN; ++j) x[j] = buf[rd + j];
+    lds_fence();
+  }
+}
+
+// The epilogue of an output kind chosen at run time; RK and Galerkin stages (kinds
+// 3 and 4) are single-plan launches only.
+template <class LY, bool SINGLE>
+__device__ __forceinline__ void finish_any(const KernelArgs& a, int64_t cell, const float* fv, double* q, int lane) {
+  if (a.out_kind == 0) finish_cell<0, LY>(a, cell, fv, q, lane);
+  else if (a.out_kind == 1) finish_cell<1, LY>(a, cell, fv, q, lane);
+  else if (!SINGLE || a.out_kind == 2) finish_cell<2, LY>(a, cell, fv, q, lane);
+  else if constexpr (SINGLE) {
+    if (a.out_kind == 3) finish_cell<3, LY>(a, cell, fv, q, lane);
+    else finish_cell<4, LY>(a, cell, fv, q, lane);
+  }
+}
+
+// Cells first, first + stride, ... (per wavefront). lds: this wavefront's
+// FftGrid<NN>::kWaveBytes. With `split` (wavefront-uniform) the four wavefronts
+// of a workgroup share each cell's transforms: every wavefront computes the
+// spectrum, wavefront wv takes the groups of T transforms wv, wv + 4, ...; the
+// partial sums meet in LDS and wavefront 0 adds them in the order 0, 1, 2, 3.
+template <int NN, bool SINGLE>
+__device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int64_t stride, bool split, int wv,
+                                         double* lds) {
+  using F = FftGrid<NN>;
+  constexpr int G = F::G, T = F::T, H = F::H, V = F::V;
+  double2* fh = reinterpret_cast<double2*>(lds);   // f_hat[k2][k1], k1 = 0 .. N/2
+  double* buf = lds + F::kFh;
+  const int g0 = split ? wv : 0, gs = split ? 4 : 1;
+  for (int64_t cell = first; cell < a.cells; cell += stride) {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int t = lane / G, r = lane & (G - 1);
+    const int c = r < NN ? r : 0;
+    const float* fc = a.f + cell * static_cast<int64_t>(NN * NN);
+    double xr[NN], xi[NN];
+    // ---- forward: along axis 0 (lane = column), transpose, along axis 1 (lane = row k1)
+#pragma unroll
+    for (int v = 0; v < NN; ++v) {
+      xr[v] = static_cast<double>(fc[v * NN + c]);
+      xi[v] = 0.0;
+    }
+    dft<NN, -1>(xr, xi);
+    transpose<NN>(xr, buf, lane);
+    transpose<NN>(xi, buf, lane);
+    dft<NN, -1>(xr, xi);
+    if (lane < H) {
+#pragma unroll
+      for (int v = 0; v < NN; ++v) fh[v * H + lane] = make_double2(xr[v], xi[v]);
+    }
+    lds_fence();
+
+    double gain[NN];
+#pragma unroll
+    for (int v = 0; v < NN; ++v) gain[v] = 0.0;
+    const int kap = r < H ? r : (r < NN ? NN - r : 0);                       // the row's partner in 0 .. N/2
+    const int neg = (r >= H && r < NN) ? static_cast<int>(0x80000000u) : 0;  // conjugate row
+    // The filter values stream from L2 in batches of four registers, two batches
+    // ahead of their use (the first two of a group before the second pass of the
+    // group before it), the spectrum from LDS one batch ahead. The scheduling
+    // barriers keep the loads of all batches from being issued together, which
+    // would spill the gain.
+    constexpr int B = 4, NB = (NN + B - 1) / B;
+    double2 m[NB][B];
+    auto load_m = [&](int b, int g) {
+      const int q = g * T + t;
+      const unsigned off = static_cast<unsigned>(((q < a.P ? q : a.P) * (NN * H) + kap) * 16);
+      const char* ft = reinterpret_cast<const char*>(a.filt);
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const int v = b * B + j;
+        if (v < NN && v != NN / 2) m[b][j] = *reinterpret_cast<const double2*>(ft + v * H * 16 + off);
+      }
+    };
+    // both passes of the transforms of group g; the first filter values of group gn
+    // are loaded on the way
+    auto transform = [&](int g, int gn) {
+      double2 z[NB][B];
+      auto load_z = [&](int b) {
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+          const int v = b * B + j;
+          if (v < NN && v != NN / 2) z[b][j] = fh[v * H + kap];
+        }
+      };
+#pragma unroll
+      for (int b = 0; b < NB; ++b) load_m(b, g);
+      load_z(0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        if (b + 1 < NB) load_z(b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+          const int v = b * B + j;
+          if (v >= NN) continue;
+          if (v == NN / 2) {   // no Nyquist content in any filter
+            xr[v] = xi[v] = 0.0;
+            continue;
+          }
+          const double my = flip(m[b][j].y, neg);
+          xr[v] = fma(m[b][j].x, z[b][j].x, -(my * z[b][j].y));
+          xi[v] = fma(m[b][j].x, z[b][j].y, my * z[b][j].x);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      dft<NN, 1>(xr, xi);
+      transpose<NN>(xr, buf, lane);
+      transpose<NN>(xi, buf, lane);
+#pragma unroll
+      for (int v = H; v < NN; ++v) xi[v] = -xi[v];
+      dft<NN, 1>(xr, xi);
+    };
+    const int full = a.P / T;   // groups of gain transforms only; the group after them ends with the loss
+    int g = g0;
+#pragma unroll 1
+    for (; g < full; g += gs) {
+      transform(g, g + gs < full ? g + gs : full);
+#pragma unroll
+      for (int v = 0; v < NN; ++v) gain[v] = fma(xr[v], xi[v], gain[v]);
+    }
+    if (g == full) {   // wavefront-uniform
+      transform(full, full);
+      const int q = full * T + t;
+      const bool is_gain = q < a.P, is_loss = q == a.P;   // (neither: an idle slot)
+      constexpr int C = 8;
+      float fl[2][C];
+      auto load_f = [&](int b) {
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          const int v = b * C + j;
+          if (v < NN) fl[b & 1][j] = fc[v * NN + c];
+        }
+      };
+      load_f(0);
+#pragma unroll
+      for (int b = 0; b * C < NN; ++b) {
+        if ((b + 1) * C < NN) load_f(b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          const int v = b * C + j;
+          if (v >= NN) continue;
+          asm volatile("" : "+v"(fl[b & 1][j]));   // loaded by every lane, selected below
+          const double x = is_loss ? -static_cast<double>(fl[b & 1][j]) : 0.0;
+          gain[v] = fma(xr[v], is_gain ? xi[v] : x, gain[v]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    // ---- add the slots: lane (t, c) keeps rows t V .. t V + V - 1 of column c
+    double sum[V];
+    if constexpr (T == 2) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        double p = gain[v], s = v + V < NN ? gain[v + V] : 0.0;
+        swap32(p, s);
+        sum[v] = p + s;
+      }
+    } else {
+      double half[2 * V];
+#pragma unroll
+      for (int v = 0; v < 2 * V; ++v) {
+        double p = v < NN ? gain[v] : 0.0, s = v + 2 * V < NN ? gain[v + 2 * V] : 0.0;
+        swap32(p, s);
+        half[v] = p + s;
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        double p = half[v], s = half[v + V];
+        swap16(p, s);
+        sum[v] = p + s;
+      }
+    }
+    if (split) {
+      double* part = buf;
+#pragma unroll
+      for (int v = 0; v < V; ++v) part[v * 64 + lane] = sum[v];
+      __syncthreads();
+      if (wv == 0) {
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+#pragma unroll
+          for (int v = 0; v < V; ++v) sum[v] += part[k * (F::kWaveBytes / 8) + v * 64 + lane];
+      }
+    }
+    if (!split || wv == 0) {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        if (F::row(v, lane) >= NN || r >= NN) sum[v] = 0.0;
+      float fv[V];
+      if (a.out_kind == 2 || a.out_kind == 3) {
+        load_cell<F>(a, cell, lane, fv, static_cast<float>(sum[0]));
+      } else {
+#pragma unroll
+        for (int v = 0; v < V; ++v) fv[v] = 0.0f;
+      }
+      finish_any<F, SINGLE>(a, cell, fv, sum, lane);
+    }
+    if (split) __syncthreads();   // the buffers are rewritten by the next cell
+  }
+}
+
+// Grid sizes with a body: every even size up to 32.
+#define QCOLL_FFT_SIZES(X) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(22) X(24) X(26) X(28) X(30) X(32)
+
+// LDS of a wavefront for grid size n.
+inline int fft_wave_bytes(int n) {
+  switch (n) {
+#define QCOLL_FFT_BYTES(N) \
+  case N: return FftGrid<N>::kWaveBytes;
+    QCOLL_FFT_SIZES(QCOLL_FFT_BYTES)
+#undef QCOLL_FFT_BYTES
+    default: return 0;
+  }
+}
+
+}  // namespace
+}  // namespace qcoll

@@ -13,7 +13,8 @@ struct KernelArgs {
   int64_t cells = 0;
   int n = 0;                    // grid points per axis (<= the kernel's tile size N)
   const void* econst = nullptr; // per-lane DFT-matrix operands (layout set by the variant)
-  const double* filt = nullptr; // FX16 filters scaled by 2^-filt_exp (layout set by the tile family)
+  const double* filt = nullptr; // FX16 filters: FFT kernels [q][k2][k1 <= n/2]; matrix kernels scaled by
+                                // 2^-filt_exp (layout set by the tile family)
   const int* filt_exp = nullptr;
   const double* loss = nullptr; // FX16: [64 lanes][16 modes], scaled by 2^-loss_exp
   int loss_exp = 0;
@@ -41,10 +42,11 @@ struct KernelArgs {
   int64_t rk_stride = 0;
   int rk_scheme = 0;
   int rk_stage = 0;
-  int tile = 32;                // MFMA tile of the kernel: 16, 32 or 64
+  int tile = 32;                // tile family of the grid: 16, 32 or 64
+  int fft = 0;                  // 1: the FP64 FFT kernels (filt in their layout), 0: the matrix kernels
   int precision = 4;            // 1 FP32, 4 FX16
   // Transform split (the latency form of batched launches): 1, or the number of
-  // workers that share a cell's transforms (32x32 FX16 tiles: 4 wavefronts of
+  // workers that share a cell's transforms (FX16 up to 32 points: 4 wavefronts of
   // one workgroup; tile 64: 2 or 4 workgroups, which leave their partial
   // results in split_ws, [cell][part][wavefront][16][64] doubles, and count
   // their arrivals in split_cnt[cell], zero between launches: the last to
@@ -113,6 +115,7 @@ struct Args3 {
 int launch_3d(const Args3& args, hipStream_t stream);
 
 // Single-plan launches (args.tile selects the 16x16 or 32x32 kernel family).
+int launch_fft(const KernelArgs& args, hipStream_t stream);   // args.fft, up to 32 points
 int launch_2d16(const KernelArgs& args, hipStream_t stream);
 int launch_2d32(const KernelArgs& args, hipStream_t stream);
 int launch_2d64(const KernelArgs& args, hipStream_t stream);

@@ -146,7 +146,7 @@ __device__ __forceinline__ const double* exp_consts() {
 // reductions) and store Q as double, or apply the stage update to f.
 // RG: rows per group of the stage update's loads (register budget of the caller).
 template <int OUT, class LY, int RG = 4>
-__device__ void finish_cell(const KernelArgs& a, int64_t cell, const float* fv, double* q, int lane) {
+__device__ __forceinline__ void finish_cell(const KernelArgs& a, int64_t cell, const float* fv, double* q, int lane) {
   if constexpr (OUT < 0) {  // epilogue chosen at run time (batched launches: eval, projection, step)
     if (a.out_kind == 0) finish_cell<0, LY>(a, cell, fv, q, lane);
     else if (a.out_kind == 1) finish_cell<1, LY>(a, cell, fv, q, lane);
@@ -299,6 +299,7 @@ __device__ void finish_cell(const KernelArgs& a, int64_t cell, const float* fv, 
       asm volatile("" : "+v"(cc) : "v"(chain));   // else all groups' loads are hoisted together
 #pragma unroll
       for (int j = 0; j < kC; ++j) {
+        if (v0 + j >= kV) continue;   // the last group of a row count that is no multiple of kC
         const int r = LY::row(v0 + j, lane);
         fn[j] = load_or_zero(fnp, r < n && cc < n, r * n + cc);
       }
@@ -309,6 +310,7 @@ __device__ void finish_cell(const KernelArgs& a, int64_t cell, const float* fv, 
         const float* Qp = a.rk_work + (S - 3 + m) * a.rk_stride + base;
 #pragma unroll
         for (int j = 0; j < kC; ++j) {
+          if (v0 + j >= kV) continue;
           const int r = LY::row(v0 + j, lane);
           const bool in = r < n && cc < n;
           if (m >= 2) Fs[m - 1][j] = load_or_zero(Fp, in, r * n + cc);
@@ -318,6 +320,7 @@ __device__ void finish_cell(const KernelArgs& a, int64_t cell, const float* fv, 
 #pragma unroll
       for (int j = 0; j < kC; ++j) {
         const int v = v0 + j;
+        if (v >= kV) continue;
         const int r = LY::row(v, lane);
         const double fnv = static_cast<double>(fn[j]);
         const double M = cM * __shfl(e1, r) * e2;

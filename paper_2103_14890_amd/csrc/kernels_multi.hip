@@ -11,6 +11,7 @@
 
 #include <cstdint>
 
+#include "body_fft.hpp"
 #include "body_t16.hpp"
 #include "body_t32.hpp"
 #include "body_t64.hpp"
@@ -24,6 +25,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
   int s = 0;
 #pragma unroll 1
   while (s + 1 < m.nslots && b >= m.block_start[s + 1]) ++s;
+  s = __builtin_amdgcn_readfirstlane(s);
   const KernelArgs& a = m.slot[s];
   if (a.tile == 64) {  // one cell (or one part of one, in the split form) per workgroup of four wavefronts
     const int64_t first = b - m.block_start[s], stride = m.block_start[s + 1] - m.block_start[s];
@@ -33,6 +35,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
     } else {
       if (a.precision == 4) t64_body<-1, true>(a, first, stride, lds);
       else t64_body<-1, false>(a, first, stride, lds);
+    }
+    return;
+  }
+  if (a.fft) {  // a wavefront per cell, or in the split form the workgroup's four wavefronts
+    const bool split = a.split > 1;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wpb = blockDim.x >> 6;
+    const int64_t b0 = b - m.block_start[s], nb = m.block_start[s + 1] - m.block_start[s];
+    double* l = reinterpret_cast<double*>(lds);
+    switch (a.n) {
+#define QCOLL_FFT_BODY(N)                                                                      \
+  case N:                                                                                      \
+    fft_body<N, false>(a, split ? b0 : b0 * wpb + w, split ? nb : nb * wpb, split, w,          \
+                       l + w * (FftGrid<N>::kWaveBytes / 8));                                  \
+    break;
+      QCOLL_FFT_SIZES(QCOLL_FFT_BODY)
+#undef QCOLL_FFT_BODY
+      default: break;
     }
     return;
   }
@@ -68,15 +87,24 @@ int launch_multi(const MultiArgs& args, int waves_per_block, hipStream_t stream)
   for (int i = 0; i < args.nslots; ++i) t64 |= args.slot[i].tile == 64;
   if (t64 && waves_per_block != 4) return -4;   // the tile-64 body needs four wavefronts per workgroup
   // dynamic LDS above the 64 KB default: 76 KB for four wavefronts of N <= 32
-  // cells, 79 KB for a tile-64 cell
-  constexpr int kMaxLds = kT64LdsBytes > kEoLdsBytes + 4 * kFhatLdsBytes ? kT64LdsBytes
-                                                                          : kEoLdsBytes + 4 * kFhatLdsBytes;
+  // cells (both kernel families), 79 KB for a tile-64 cell
+  constexpr int kT32LdsBytes = kEoLdsBytes + 4 * kFhatLdsBytes;
   static const bool attr_ok = [] {
+    int most = kT64LdsBytes > kT32LdsBytes ? kT64LdsBytes : kT32LdsBytes;
+    for (int n = 4; n <= 32; n += 2) most = most > 4 * fft_wave_bytes(n) ? most : 4 * fft_wave_bytes(n);
     return hipFuncSetAttribute(reinterpret_cast<const void*>(multi_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kMaxLds) == hipSuccess;
+                               most) == hipSuccess;
   }();
   if (!attr_ok) return -3;
-  const int lds_bytes = t64 ? kMaxLds : kEoLdsBytes + kFhatLdsBytes * waves_per_block;
+  int lds_bytes = 0;
+  for (int i = 0; i < args.nslots; ++i) {
+    const KernelArgs& a = args.slot[i];
+    const int need = a.fft ? waves_per_block * fft_wave_bytes(a.n)
+                     : a.tile == 64 ? kT64LdsBytes
+                     : a.tile == 32 && a.precision == 4 ? kEoLdsBytes + kFhatLdsBytes * waves_per_block
+                                                        : 0;
+    if (need > lds_bytes) lds_bytes = need;
+  }
   hipLaunchKernelGGL(multi_kernel, dim3(static_cast<unsigned>(blocks)), dim3(64 * waves_per_block), lds_bytes, stream,
                      args);
   return hipGetLastError() == hipSuccess ? 0 : -3;

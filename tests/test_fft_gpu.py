@@ -1,0 +1,55 @@
+"""The FP64 FFT kernels (FX16 plans without the projection) on every grid size they
+have a body for, against the FP64 oracle.
+
+Tolerance: spectra, transforms and sums are FP64 (their error relative to Q is of
+the order of gain/Q x 1e-15 ~ 1e-13), so the float rounding of Q is what is left:
+at most 2^-24 = 6e-8 of every value, hence of the 2-norm; 1.5e-7 leaves room for
+the plan's filters, which the oracle computes separately.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle import spectral as sp
+from oracle import stepping
+from paper_2103_14890_amd import qcoll
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+SIZES = list(range(4, 33, 2))
+
+
+def _case(N, cells):
+    kernel = "maxwell" if N % 8 == 2 else "hard_sphere"
+    L = 3.0 + 0.16 * N
+    f = wl.mixture_cells(2, N, L, cells, 50 + N).astype(np.float32)
+    # a different scale per cell, so that a mixed-up cell or slot shows
+    f *= np.linspace(0.5, 2.0, cells, dtype=np.float32)[:, None, None]
+    M = 6 if N % 4 == 0 else 8
+    s = sp.Setup(d=2, N=N, L=L, kernel=kernel, M=M)
+    return f, L, kernel, M, sp.q_fast(f.astype(np.float64), s)
+
+
+def _rel(got, ref):
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("N", SIZES)
+def test_every_grid_size(N):
+    f, L, kernel, M, ref = _case(N, 7)   # 7 cells: the last workgroup is not full
+    plan = qcoll.Plan(2, N, L, kernel, M)
+    t = torch.tensor(f, device=DEV)
+    for waves in (1, 4):
+        plan.set_launch(waves, 1 if waves == 4 else 1 << 20)   # one workgroup walking the cells, or one per cell
+        q = plan.eval(t).cpu().double().numpy()
+        assert _rel(q, ref) < 1.5e-7, (N, waves)
+    one = plan.eval(t[2:3].contiguous()).cpu().numpy()
+    assert np.array_equal(one, q[2:3].astype(np.float32)), "a cell's result does not depend on the batch"
+    status = torch.full((7,), -1, dtype=torch.int32, device=DEV)
+    g = plan.step(t.clone(), 0.01, 1.0, "imex", status=status).cpu().double().numpy()
+    want = stepping.imex_euler_penalized(f.astype(np.float64), ref, 0.01, 1.0, 2, L)
+    assert np.abs(g - want).max() <= 1.2e-7 * np.abs(want).max()
+    assert status.cpu().tolist() == [0] * 7
+    plan.close()
