@@ -53,8 +53,8 @@ enum { QCOLL_MAXWELL = 0, QCOLL_HARD_SPHERE = 1, QCOLL_VHS = 2 };
  *                  exactly in the FP32 accumulator, plus an FP16 hi/lo
  *                  remainder (six products, two accumulators); spectra,
  *                  filters and all elementwise work in FP64. 2D plans without
- *                  QCOLL_CONSERVE and QCOLL_GALERKIN on grids of up to 32 points
- *                  per axis compute the DFTs as FFTs in FP64 instead (results
+ *                  QCOLL_CONSERVE and QCOLL_GALERKIN on grids of up to 32, or of
+ *                  36, 40, .. 64 points per axis compute the DFTs as FFTs in FP64 instead (results
  *                  within the same bounds, the transforms exact to FP64). */
 enum { QCOLL_FP32 = 1, QCOLL_MIX_FX16 = 4 };
 

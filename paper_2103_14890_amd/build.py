@@ -19,7 +19,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libqcoll.so")
 
 HOST_SOURCES = ["plan.cpp", "api.cpp", "transport.cpp"]
-DEVICE_SOURCES = ["kernels_fft.hip", "kernels_2d.hip", "kernels_2d16.hip", "kernels_2d64.hip", "kernels_multi.hip", "kernels_3d.hip",
+DEVICE_SOURCES = ["kernels_multi.hip", "kernels_fft.hip", "kernels_fft64.hip", "kernels_2d.hip", "kernels_2d16.hip", "kernels_2d64.hip", "kernels_3d.hip",
                   "kernels_galerkin.hip", "kernels_transport.hip", "kernels_classical.hip", "noalloc.hip"]
 ARCH = "gfx950"
 

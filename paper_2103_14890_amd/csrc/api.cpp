@@ -336,29 +336,56 @@ void swap_tile_tables(qcoll_plan_s* p) {
 }
 
 int launch(const qcoll::KernelArgs& a, hipStream_t stream) {
-  if (a.fft) return qcoll::launch_fft(a, stream);
+  if (a.fft) return a.tile == 64 ? qcoll::launch_fft64(a, stream) : qcoll::launch_fft(a, stream);
   if (a.tile == 64) return qcoll::launch_2d64(a, stream);
   return a.tile == 32 ? qcoll::launch_2d32(a, stream) : qcoll::launch_2d16(a, stream);
 }
 
-// Plans that run on the FP64 FFT kernels: FX16 without the projection, up to 32
-// points per axis. Measured against the split-FP16 matrix kernels (4096 cells, M =
+// Plans that run on the FP64 FFT kernels: FX16 without the projection, on grids of
+// up to 32 points per axis and of 36, 40, .. 64 (the workgroup kernel splits a line
+// in four). Measured against the split-FP16 matrix kernels (4096 cells, M =
 // 8, hard spheres, float Q): 20 points 195 -> 80 us, 24 points 201 -> 99, 32 points
-// 216 -> 145; 10000 cells of 16 points 101 -> 73 (Maxwell, M = 16: 48.6 -> 45.5).
+// 216 -> 145; 10000 cells of 16 points 101 -> 73 (Maxwell, M = 16: 48.6 -> 45.5);
+// 4000 cells of 48 points 1227 -> 656, of 64 points 1318 -> 962.
 // Plans with the projection stay on the matrix kernels: their double Q carries the
 // digits of that arithmetic below 1e-6, and callers compare it with earlier
 // results at double precision. So do the fine grids of Galerkin plans.
 bool fft_supported(const qcoll_plan_s* p) {
   return p->hp.d == 2 && p->precision == QCOLL_MIX_FX16 && !(p->flags & QCOLL_CONSERVE) && !p->galerkin &&
-         p->hp.N <= 32;
+         (p->hp.N <= 32 || p->hp.N % 4 == 0);
 }
 
 // Filter table of the FFT kernels. Entry q < P is the packed multiplier of gain
 // transform q, entry P the loss multiplier. The multipliers are even,
-// m(-k) = m(k), so half of the rows are held: [q][k2][k1 = 0 .. N/2], complex.
+// m(-k) = m(k), so half of the rows are held: [q][k2][k1 = 0 .. N/2], complex. Above
+// 32 points: the classes k2 mod 4 = 0, 1, 2 (class 3 mirrors class 1), each as
+// [n1 = k2 / 4][k1 of 64 lanes], and the roots w^(i j), i < 4, j < 16.
 int build_device_fft(qcoll_plan_s* p) {
   const auto& hp = p->hp;
   const int n = hp.N, P = static_cast<int>(hp.packed.size());
+  if (n > 32) {
+    const int R = n / 4;
+    std::vector<double> ft(static_cast<size_t>(P + 1) * 3 * R * 64 * 2, 0.0);
+    for (int q = 0; q <= P; ++q)
+      for (int cls = 0; cls < 3; ++cls)
+        for (int n1 = 0; n1 < R; ++n1)
+          for (int k1 = 0; k1 < n; ++k1) {
+            const int64_t k = static_cast<int64_t>(k1) * n + 4 * n1 + cls;
+            const std::complex<double> m = q < P ? hp.packed[q][k] : std::complex<double>(hp.loss_scaled[k], 0.0);
+            const size_t o = (((static_cast<size_t>(q) * 3 + cls) * R + n1) * 64 + k1) * 2;
+            ft[o] = m.real();
+            ft[o + 1] = m.imag();
+          }
+    if (int rc = upload(ft, &p->filt, p->device_bytes)) return rc;
+    std::vector<double> tw(4 * 16 * 2, 0.0);
+    for (int i = 0; i < 4; ++i)
+      for (int j = 0; j < 16; ++j) {
+        const double ang = 2.0 * kPi * static_cast<double>((i * j) % n) / n;
+        tw[(i * 16 + j) * 2] = std::cos(ang);
+        tw[(i * 16 + j) * 2 + 1] = std::sin(ang);
+      }
+    return upload(tw, &p->tw, p->device_bytes);
+  }
   const int H = n / 2 + 1;
   std::vector<double> ft(static_cast<size_t>(P + 1) * n * H * 2);
   size_t o = 0;

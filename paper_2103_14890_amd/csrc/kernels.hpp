@@ -13,12 +13,12 @@ struct KernelArgs {
   int64_t cells = 0;
   int n = 0;                    // grid points per axis (<= the kernel's tile size N)
   const void* econst = nullptr; // per-lane DFT-matrix operands (layout set by the variant)
-  const double* filt = nullptr; // FX16 filters: FFT kernels [q][k2][k1 <= n/2]; matrix kernels scaled by
+  const double* filt = nullptr; // FX16 filters: FFT kernels (layout set by the grid); matrix kernels scaled by
                                 // 2^-filt_exp (layout set by the tile family)
   const int* filt_exp = nullptr;
   const double* loss = nullptr; // FX16: [64 lanes][16 modes], scaled by 2^-loss_exp
   int loss_exp = 0;
-  const double* tw = nullptr;   // tile-64 kernel: w^(k p), [p in {0,1}][k < 32][re, im]
+  const double* tw = nullptr;   // tile-64 matrix kernel: w^(k p), [p in {0,1}][k < 32][re, im]; FFT: w^(i j), [4][16][re, im]
   const float* filt32 = nullptr;  // FP32: [P][64][16][re, im]
   const float* loss32 = nullptr;  // FP32: [64][16]
   int P = 0;                    // packed gain transforms
@@ -115,7 +115,8 @@ struct Args3 {
 int launch_3d(const Args3& args, hipStream_t stream);
 
 // Single-plan launches (args.tile selects the 16x16 or 32x32 kernel family).
-int launch_fft(const KernelArgs& args, hipStream_t stream);   // args.fft, up to 32 points
+int launch_fft(const KernelArgs& args, hipStream_t stream);    // args.fft, up to 32 points
+int launch_fft64(const KernelArgs& args, hipStream_t stream);  // args.fft, 36, 40, .. 64 points
 int launch_2d16(const KernelArgs& args, hipStream_t stream);
 int launch_2d32(const KernelArgs& args, hipStream_t stream);
 int launch_2d64(const KernelArgs& args, hipStream_t stream);

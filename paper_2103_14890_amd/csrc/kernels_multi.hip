@@ -12,6 +12,7 @@
 #include <cstdint>
 
 #include "body_fft.hpp"
+#include "body_fft64.hpp"
 #include "body_t16.hpp"
 #include "body_t32.hpp"
 #include "body_t64.hpp"
@@ -27,6 +28,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void m
   while (s + 1 < m.nslots && b >= m.block_start[s + 1]) ++s;
   s = __builtin_amdgcn_readfirstlane(s);
   const KernelArgs& a = m.slot[s];
+  if (a.fft && a.tile == 64) {   // one cell (or part of one) per workgroup of four wavefronts
+    const int64_t first = b - m.block_start[s], stride = m.block_start[s + 1] - m.block_start[s];
+    switch (a.n) {
+#define QCOLL_FFT64_BODY(R) \
+  case 4 * R: fft64_body<R, false>(a, first, stride, lds); break;
+      QCOLL_FFT64_SIZES(QCOLL_FFT64_BODY)
+#undef QCOLL_FFT64_BODY
+      default: break;
+    }
+    return;
+  }
   if (a.tile == 64) {  // one cell (or one part of one, in the split form) per workgroup of four wavefronts
     const int64_t first = b - m.block_start[s], stride = m.block_start[s + 1] - m.block_start[s];
     if (a.split > 1) {
@@ -87,7 +99,8 @@ int launch_multi(const MultiArgs& args, int waves_per_block, hipStream_t stream)
   for (int i = 0; i < args.nslots; ++i) t64 |= args.slot[i].tile == 64;
   if (t64 && waves_per_block != 4) return -4;   // the tile-64 body needs four wavefronts per workgroup
   // dynamic LDS above the 64 KB default: 76 KB for four wavefronts of N <= 32
-  // cells (both kernel families), 79 KB for a tile-64 cell
+  // cells (both kernel families), 79 KB for a tile-64 cell of the matrix kernels, 67 KB
+  // of the FFT kernels
   constexpr int kT32LdsBytes = kEoLdsBytes + 4 * kFhatLdsBytes;
   static const bool attr_ok = [] {
     int most = kT64LdsBytes > kT32LdsBytes ? kT64LdsBytes : kT32LdsBytes;
@@ -99,7 +112,8 @@ int launch_multi(const MultiArgs& args, int waves_per_block, hipStream_t stream)
   int lds_bytes = 0;
   for (int i = 0; i < args.nslots; ++i) {
     const KernelArgs& a = args.slot[i];
-    const int need = a.fft ? waves_per_block * fft_wave_bytes(a.n)
+    const int need = a.fft && a.tile == 64 ? Fft64<16>::kLdsBytes
+                     : a.fft ? waves_per_block * fft_wave_bytes(a.n)
                      : a.tile == 64 ? kT64LdsBytes
                      : a.tile == 32 && a.precision == 4 ? kEoLdsBytes + kFhatLdsBytes * waves_per_block
                                                         : 0;
