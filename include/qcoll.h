@@ -196,8 +196,9 @@ int qcoll_eval_galerkin(qcoll_plan_t plan, const float* f, void* Q, int64_t cell
  *   F_l = [f^n + (dt/eps) sum_{m<l} (At_lm G_m + A_lm S_m) + A_ll (dt/eps) nu M]
  *         / (1 + A_ll dt nu / eps),   S_m = nu (M - F_m), G_m = Q(F_m) - S_m,
  * and f^{n+1} = F_S (both tableaux are stiffly accurate). Each stage l is one
- * launch that evaluates Q(F_{l-1}) and forms F_l. scheme: QCOLL_IMEX_ARS222
- * (S = 3, two launches) or QCOLL_IMEX_BPR343 (S = 5, four launches). work:
+ * launch that evaluates Q(F_{l-1}) and forms F_l; the last stage of BPR(3,4,3)
+ * takes no Q(F_4) and is formed with stage 4. scheme: QCOLL_IMEX_ARS222
+ * (S = 3, two launches) or QCOLL_IMEX_BPR343 (S = 5, three launches). work:
  * device float buffer owned by the caller, at least qcoll_step_rk_work_bytes()
  * bytes, holding the stage values and Q of earlier stages (FP32) and, per
  * cell, four FP64 moments of f^n (written by the first launch of the step,

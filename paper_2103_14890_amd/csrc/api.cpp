@@ -947,6 +947,8 @@ int qcoll_step_ws(qcoll_plan_t p, float* f, int64_t cells, double dt, double eps
 }
 
 namespace {
+// Stage launches end at this stage: the launch of stage 4 of BPR(3,4,3) forms stage 5 too.
+int rk_last_launch(int scheme) { return scheme == QCOLL_IMEX_ARS222 ? 3 : 4; }
 int rk_stages(int scheme) { return scheme == QCOLL_IMEX_ARS222 ? 3 : (scheme == QCOLL_IMEX_BPR343 ? 5 : 0); }
 }  // namespace
 
@@ -1011,7 +1013,7 @@ int qcoll_step_rk(qcoll_plan_t p, float* f, int64_t cells, double dt, double eps
   if (!f || !work || work_bytes < qcoll_step_rk_work_bytes(p, scheme, cells)) return QCOLL_EINVAL;
   const int64_t stride = cells * static_cast<int64_t>(p->hp.N) * p->hp.N * (p->hp.d == 3 ? p->hp.N : 1);
   if (p->hp.d == 3) {
-    for (int l = 2; l <= S; ++l) {
+    for (int l = 2; l <= rk_last_launch(scheme); ++l) {
       qcoll::Slot3 s3 = make_slot3(p);
       s3.f = l == 2 ? f : work + static_cast<int64_t>(l - 3) * stride;  // stage input F_{l-1}
       s3.dt_eps = dt / eps;
@@ -1029,7 +1031,7 @@ int qcoll_step_rk(qcoll_plan_t p, float* f, int64_t cells, double dt, double eps
   }
   const uintptr_t mom_at = reinterpret_cast<uintptr_t>(work + static_cast<int64_t>(2 * S - 3) * stride);
   double* mom = reinterpret_cast<double*>((mom_at + 7) & ~static_cast<uintptr_t>(7));
-  for (int l = 2; l <= S; ++l) {
+  for (int l = 2; l <= rk_last_launch(scheme); ++l) {
     qcoll::KernelArgs a = make_args(p);
     a.f = l == 2 ? f : work + static_cast<int64_t>(l - 3) * stride;  // stage input F_{l-1}
     a.cells = cells;

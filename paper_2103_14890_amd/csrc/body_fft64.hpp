@@ -127,7 +127,11 @@ __device__ __forceinline__ void finish_rows(const KernelArgs& a, int64_t cell, d
     int sch = a.rk_scheme - 1, l = a.rk_stage;
     asm volatile("" : "+s"(sch), "+s"(l));   // the tableau is read here, per cell
     const int St = sch == 0 ? 3 : 5;
-    last = l == St;
+    const bool both = sch == 1 && l == 4;   // the last two stages of BPR(3,4,3)
+    last = l == St || both;
+    const double* At5 = kRkAt[1][4];
+    const double* Dd5 = kRkD[1][4];
+    const double A55 = kRkA[1][4][4];
     const double* At = kRkAt[sch][l - 1];
     const double* Ai = kRkA[sch][l - 1];
     const double* Dd = kRkD[sch][l - 1];
@@ -154,7 +158,7 @@ __device__ __forceinline__ void finish_rows(const KernelArgs& a, int64_t cell, d
     const double Tm = 0.5 * (s[3] / s[0] - u1 * u1 - u2 * u2);
     const double nu = rho, k = a.dt_eps;
     const double cM = rho / (2.0 * 3.14159265358979323846 * Tm);
-    const double rden = 1.0 / (1.0 + Ai[l - 1] * k * nu);
+    const double rden = 1.0 / (1.0 + Ai[l - 1] * k * nu), rden5 = 1.0 / (1.0 + A55 * k * nu);
     const double* ec = exp_consts();
     const double e2 = exp_nonpos(-(v2 - u2) * (v2 - u2) / (2.0 * Tm), ec);
     const double vr = -a.L + a.dv * (w + 4 * (lane % R));   // the factor of row w + 4 (lane mod R)
@@ -164,7 +168,7 @@ __device__ __forceinline__ void finish_rows(const KernelArgs& a, int64_t cell, d
       const int o = (w + 4 * b) * N + c;
       const double fnv = static_cast<double>(fnp[o]);
       const double M = cM * __shfl(e1, b) * e2;
-      double t1 = Ai[l - 1] * M, t2 = 0.0;
+      double t1 = Ai[l - 1] * M, t2 = 0.0, w1 = A55 * M, w2 = 0.0;
 #pragma unroll
       for (int m = 1; m <= 4; ++m) {
         if (m >= l) break;   // uniform
@@ -172,13 +176,16 @@ __device__ __forceinline__ void finish_rows(const KernelArgs& a, int64_t cell, d
                           : (m == l - 1 ? static_cast<double>(fv[b])
                                         : static_cast<double>(__builtin_nontemporal_load(&a.rk_work[(m - 2) * a.rk_stride + base + o])));
         t1 += Dd[m - 1] * (M - Fm);
-        if (At[m - 1] != 0.0) {
+        if (both) w1 += Dd5[m - 1] * (M - Fm);
+        if (At[m - 1] != 0.0) {   // (the same terms in stages 4 and 5 of BPR(3,4,3))
           const double Qm =
               m == l - 1 ? q[b] : static_cast<double>(__builtin_nontemporal_load(&a.rk_work[(St - 3 + m) * a.rk_stride + base + o]));
           t2 += At[m - 1] * Qm;
+          if (both) w2 += At5[m - 1] * Qm;
         }
       }
-      const float Fl = static_cast<float>((fnv + k * (nu * t1 + t2)) * rden);
+      float Fl = static_cast<float>((fnv + k * (nu * t1 + t2)) * rden);
+      if (both) Fl = static_cast<float>((fnv + k * (nu * (w1 + Dd5[3] * (M - static_cast<double>(Fl))) + w2)) * rden5);
       if (!in) continue;
       if (last) {
         bad |= !(fabsf(Fl) <= 3.0e38f);

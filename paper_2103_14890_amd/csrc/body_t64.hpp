@@ -493,6 +493,9 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       const int ns = sch == 0 ? 3 : 5;   // stages of the scheme
       const double* At = kRkAt[sch][l - 1];
       const double* Ai = kRkA[sch][l - 1];
+      const bool both = sch == 1 && l == 4;   // the last two stages of BPR(3,4,3)
+      const double* At5 = kRkAt[1][4];
+      const double* Ai5 = kRkA[1][4];
       const int64_t base = cell * static_cast<int64_t>(n) * n;
       float* fnp = a.rk_fn + base;
       // f^n is read twice (moments, then the update) instead of being held in
@@ -520,7 +523,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       const double Tm = 0.5 * (sm[3] / sm[0] - u1 * u1 - u2 * u2);
       const double nu = rho, k = a.dt_eps;
       const double cM = rho / (2.0 * 3.14159265358979323846 * Tm);
-      const double den = 1.0 + Ai[l - 1] * k * nu;
+      const double den = 1.0 + Ai[l - 1] * k * nu, den5 = 1.0 + Ai5[4] * k * nu;
       const double* ec = exp_consts();
       // the Maxwellian factors by velocity axis, M = cM e1(v1) e2(v2): this
       // lane's column factor, and the factor of this wave's row 2 (lane mod 32)
@@ -536,22 +539,25 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
         if (!(r < np && c < np)) continue;
         const int o = (2 * r + p1) * n + 2 * c + p2;
         const double fnv = static_cast<double>(fnp[o]);
-        double rhs = fnv + Ai[l - 1] * k * nu * M;
+        double rhs = fnv + Ai[l - 1] * k * nu * M, rhs5 = fnv + Ai5[4] * k * nu * M;
         for (int m = 1; m < l; ++m) {
           const double Fm = m == 1 ? fnv
                             : (m == l - 1 ? static_cast<double>(fv[v])
                                           : static_cast<double>(__builtin_nontemporal_load(&a.rk_work[(m - 2) * a.rk_stride + base + o])));
           const double Sm = nu * (M - Fm);
-          double acc = Ai[m - 1] * Sm;
+          double acc = Ai[m - 1] * Sm, acc5 = Ai5[m - 1] * Sm;
           if (At[m - 1] != 0.0) {
             const double Qm =
                 m == l - 1 ? gain[v] : static_cast<double>(__builtin_nontemporal_load(&a.rk_work[(ns - 3 + m) * a.rk_stride + base + o]));
             acc += At[m - 1] * (Qm - Sm);
+            if (both) acc5 += At5[m - 1] * (Qm - Sm);   // (the same terms in stages 4 and 5)
           }
           rhs += k * acc;
+          if (both) rhs5 += k * acc5;
         }
-        const float Fl = static_cast<float>(rhs / den);
-        if (l == ns) {
+        float Fl = static_cast<float>(rhs / den);
+        if (both) Fl = static_cast<float>((rhs5 + k * Ai5[3] * nu * (M - static_cast<double>(Fl))) / den5);
+        if (l == ns || both) {
           bad |= !(fabsf(Fl) <= 3.0e38f);
           __builtin_nontemporal_store(Fl, &fnp[o]);
         } else {
@@ -559,7 +565,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
           __builtin_nontemporal_store(static_cast<float>(gain[v]), &a.rk_work[(ns - 3 + (l - 1)) * a.rk_stride + base + o]);
         }
       }
-      if (l == ns && a.status) {
+      if ((l == ns || both) && a.status) {
         bad = __any(bad) ? 1 : 0;
         if (lane == 0) red[w * 4 + 1] = bad;
         __syncthreads();

@@ -694,6 +694,9 @@ __device__ void cell_3d(const Slot3& a, int64_t cell, char* scratch, double* red
     const int S = sch == 0 ? 3 : 5;
     const double* At = kRkAt[sch][l - 1];
     const double* Ai = kRkA[sch][l - 1];
+    const bool both = sch == 1 && l == 4;   // the last two stages of BPR(3,4,3)
+    const double* At5 = kRkAt[1][4];
+    const double* Ai5 = kRkA[1][4];
     float* fnp = a.rk_fn + base;
     double sm[5] = {0, 0, 0, 0, 0};
     for (int t = w; t < T; t += 4)
@@ -717,7 +720,7 @@ __device__ void cell_3d(const Slot3& a, int64_t cell, char* scratch, double* red
     const double nu = rho, k = a.dt_eps;
     const double tp = 2.0 * 3.14159265358979323846 * Tm;
     const double cM = rho / (tp * sqrt(tp));
-    const double den = 1.0 + Ai[l - 1] * k * nu;
+    const double den = 1.0 + Ai[l - 1] * k * nu, den5 = 1.0 + Ai5[4] * k * nu;
     const double* ec = exp_consts();
     int bad = 0;
     for (int t = w; t < T; t += 4)
@@ -730,22 +733,25 @@ __device__ void cell_3d(const Slot3& a, int64_t cell, char* scratch, double* red
         const double c2 = (v0 - u0) * (v0 - u0) + (v1 - u1) * (v1 - u1) + (v2 - u2) * (v2 - u2);
         const double M = cM * exp_nonpos(-c2 / (2.0 * Tm), ec);
         const double fn = static_cast<double>(fnp[o]);
-        double rhs = fn + Ai[l - 1] * k * nu * M;
+        double rhs = fn + Ai[l - 1] * k * nu * M, rhs5 = fn + Ai5[4] * k * nu * M;
         for (int m = 1; m < l; ++m) {
           const double Fm = m == 1 ? fn
                             : (m == l - 1 ? static_cast<double>(fc[o])
                                           : static_cast<double>(a.rk_work[(m - 2) * a.rk_stride + base + o]));
           const double Sm = nu * (M - Fm);
-          double acc = Ai[m - 1] * Sm;
+          double acc = Ai[m - 1] * Sm, acc5 = Ai5[m - 1] * Sm;
           if (At[m - 1] != 0.0) {
             const double Qm = m == l - 1 ? gain[t * T2 + r * T + x]
                                          : static_cast<double>(a.rk_work[(S - 3 + m) * a.rk_stride + base + o]);
             acc += At[m - 1] * (Qm - Sm);
+            if (both) acc5 += At5[m - 1] * (Qm - Sm);   // (the same terms in stages 4 and 5)
           }
           rhs += k * acc;
+          if (both) rhs5 += k * acc5;
         }
-        const float Fl = static_cast<float>(rhs / den);
-        if (l == S) {
+        float Fl = static_cast<float>(rhs / den);
+        if (both) Fl = static_cast<float>((rhs5 + k * Ai5[3] * nu * (M - static_cast<double>(Fl))) / den5);
+        if (l == S || both) {
           bad |= !(fabsf(Fl) <= 3.0e38f);
           fnp[o] = Fl;
         } else {
@@ -753,7 +759,7 @@ __device__ void cell_3d(const Slot3& a, int64_t cell, char* scratch, double* red
           a.rk_work[(S - 3 + (l - 1)) * a.rk_stride + base + o] = static_cast<float>(gain[t * T2 + r * T + x]);
         }
       }
-    if (l == S && a.status) {
+    if ((l == S || both) && a.status) {
       double b[1] = {static_cast<double>(__any(bad) ? 1 : 0)};
       block_sum<1>(b, red);
       if (threadIdx.x == 0) a.status[cell] = b[0] > 0.0 ? 1 : 0;

@@ -83,7 +83,9 @@ struct Lay16 {  // 16x16 MFMA result tile
 // Butcher tableaux of the multi-stage IMEX steps (section 3.4): explicit At
 // and implicit A, rows = stages. [0] ARS(2,2,2) with gamma = 1 - 1/sqrt 2 and
 // delta = 1 - 1/(2 gamma); [1] BPR(3,4,3). Both are stiffly accurate, so the
-// step's result is the last stage.
+// step's result is the last stage. In BPR(3,4,3) the last stage takes no Q of its
+// predecessor (At_54 = 0), so the launch of stage 4 forms both (the launch of
+// stage 5 would evaluate Q(F_4) for nothing: a quarter of the step's transforms).
 constexpr double kRsqrt2 = 0.70710678118654752440084436210485;
 constexpr double kGam = 1.0 - kRsqrt2;
 constexpr double kDel = 1.0 - 1.0 / (2.0 * kGam);
@@ -226,6 +228,10 @@ __device__ __forceinline__ void finish_cell(const KernelArgs& a, int64_t cell, c
     const double* At = kRkAt[sch][l - 1];
     const double* Ai = kRkA[sch][l - 1];
     const double* Dd = kRkD[sch][l - 1];
+    const bool both = sch == 1 && l == 4;   // the last two stages of BPR(3,4,3)
+    const double* At5 = kRkAt[1][4];
+    const double* Dd5 = kRkD[1][4];
+    const double A55 = kRkA[1][4][4];
     float* fnp = a.rk_fn + base;
     // The moments of f^n are the same in every stage of the step: stage 2,
     // whose input F_1 is f^n (fv, zero outside the grid), sums them and keeps
@@ -274,6 +280,7 @@ __device__ __forceinline__ void finish_cell(const KernelArgs& a, int64_t cell, c
     // weights are the tableau's own (scalar registers), and one reciprocal of
     // den per cell instead of a division per point.
     const double rden = 1.0 / (1.0 + Ai[l - 1] * k * nu);
+    const double rden5 = 1.0 / (1.0 + A55 * k * nu);
     bool useq[4];   // Q(F_m) enters the update (At_lm != 0); per cell, not per point
 #pragma unroll
     for (int m = 1; m <= 4; ++m) useq[m - 1] = At[m - 1] != 0.0;
@@ -324,23 +331,26 @@ __device__ __forceinline__ void finish_cell(const KernelArgs& a, int64_t cell, c
         const int r = LY::row(v, lane);
         const double fnv = static_cast<double>(fn[j]);
         const double M = cM * __shfl(e1, r) * e2;
-        double t1 = Ai[l - 1] * M, t2 = 0.0;
+        double t1 = Ai[l - 1] * M, t2 = 0.0, w1 = A55 * M, w2 = 0.0;
 #pragma unroll
         for (int m = 1; m <= 4; ++m) {
           if (m >= l) break;
           const double Fm = m == 1 ? fnv : (m == l - 1 ? static_cast<double>(fv[v]) : static_cast<double>(Fs[m - 1][j]));
           t1 += Dd[m - 1] * (M - Fm);
-          if (useq[m - 1]) {
+          if (both) w1 += Dd5[m - 1] * (M - Fm);
+          if (useq[m - 1]) {   // (the same terms in stages 4 and 5 of BPR(3,4,3))
             const double Qm = m == l - 1 ? q[v] : static_cast<double>(Qs[m - 1][j]);
             t2 += At[m - 1] * Qm;
+            if (both) w2 += At5[m - 1] * Qm;
           }
         }
         const double rhs = fnv + k * (nu * t1 + t2);
         chain = rhs;
         if (!(r < n && c < n)) continue;
         const int o = r * n + c;
-        const float Fl = static_cast<float>(rhs * rden);
-        if (l == S) {
+        float Fl = static_cast<float>(rhs * rden);
+        if (both) Fl = static_cast<float>((fnv + k * (nu * (w1 + Dd5[3] * (M - static_cast<double>(Fl))) + w2)) * rden5);
+        if (l == S || both) {
           bad |= !(fabsf(Fl) <= 3.0e38f);
           fnp[o] = Fl;
         } else {
@@ -349,7 +359,7 @@ __device__ __forceinline__ void finish_cell(const KernelArgs& a, int64_t cell, c
         }
       }
     }
-    if (l == S && a.status) {
+    if ((l == S || both) && a.status) {
       bad = __any(bad) ? 1 : 0;
       if ((threadIdx.x & 63) == 0) a.status[cell] = bad;
     }
