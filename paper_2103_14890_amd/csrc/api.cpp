@@ -25,8 +25,8 @@ struct qcoll_plan_s {
   double* gal_restrict = nullptr;  // [N][Nf]
   bool classical = false;
   std::vector<double> beta;        // classical plans: beta[l][m] (host, FP64)
-  double* cl_betaT = nullptr;      // device betaT[m][k] = beta((k - m) mod N, m)
-  double* cl_tw = nullptr;         // device exp(-2 pi i j / N)
+  double* cl_weights = nullptr;    // device tables of the classical kernel (ClassicalArgs)
+  double* cl_extra = nullptr;
   int precision = 0;
   unsigned flags = 0;
   int device = -1;
@@ -121,9 +121,9 @@ void free_device(qcoll_plan_s* p) {
   p->split_cnt = nullptr;
   p->split_cap = 0;
   p->split_alloc = 0;
-  hipFree(p->cl_betaT);
-  hipFree(p->cl_tw);
-  p->cl_betaT = p->cl_tw = nullptr;
+  hipFree(p->cl_weights);
+  hipFree(p->cl_extra);
+  p->cl_weights = p->cl_extra = nullptr;
   p->filt3 = nullptr;
   p->scratch = nullptr;
   p->tw = nullptr;
@@ -679,6 +679,37 @@ void classical_table(const qcoll::HostPlan& src, std::vector<double>& beta) {
   for (auto& th : pool) th.join();
 }
 
+// Device tables of the classical kernel (layout: ClassicalArgs). The kernel modes
+// are even, beta(-l, -m) = beta(l, m), so the output rows k1 = 0 .. N/2 are enough.
+int build_device_classical(qcoll_plan_s* p) {
+  const int N = p->hp.N, H = N / 2, W = qcoll::classical_row(N);
+  const int64_t n = static_cast<int64_t>(N) * N;
+  auto beta = [&](int l1, int l2, int m1, int m2) {
+    return p->beta[(static_cast<int64_t>(l1) * N + l2) * n + m1 * N + m2];
+  };
+  std::vector<double> wt(static_cast<size_t>(N) * (H + 1) * N * W, 0.0), ex(2 * n);
+  for (int j = 0; j < N; ++j) {
+    const int k1 = (j + 1) / 2, h = j == 0 || j == N - 1 ? 0 : (j + 1) & 1;
+    for (int q = 0; q <= H; ++q) {
+      if (q == H && (k1 & 1)) continue;
+      const int m1 = ((k1 + 1) / 2 + q) % N, l1 = (k1 - m1 + 2 * N) % N;
+      for (int m2 = 0; m2 < N; ++m2)
+        for (int i = 0; i < H; ++i) {
+          const int l2 = (h * H + i - m2 + N) % N;
+          double w = beta(l1, l2, m1, m2);
+          if (l1 != m1) w += beta(m1, m2, l1, l2);
+          wt[((static_cast<size_t>(j) * (H + 1) + q) * N + m2) * W + i] = w;
+        }
+    }
+  }
+  for (int e = 0; e < 2; ++e)
+    for (int m1 = 0; m1 < N; ++m1)
+      for (int m2 = 0; m2 < N; ++m2)
+        ex[(static_cast<size_t>(e) * N + m1) * N + m2] = beta((e * H - m1 + N) % N, (H - m2 + N) % N, m1, m2);
+  int rc = upload(wt, &p->cl_weights, p->device_bytes);
+  return rc ? rc : upload(ex, &p->cl_extra, p->device_bytes);
+}
+
 bool device_supported(const qcoll::HostPlan& hp, int precision) {
   if (hp.d == 3) return hp.N <= 32 && (precision == QCOLL_FP32 || precision == QCOLL_MIX_FX16);
   if (hp.d != 2) return false;
@@ -757,21 +788,7 @@ static int plan_create(qcoll_plan_t* out, int d, int n_per_dim, double L, int ke
     p->max_blocks = static_cast<int64_t>(cus) * 8;
     p->tile = p->hp.N > 32 ? 64 : (p->hp.N > 16 ? 32 : 16);
     if (p->classical) {
-      const int N = p->hp.N;
-      const int64_t n = static_cast<int64_t>(N) * N;
-      std::vector<double> bt(n * n), tw(2 * N);
-      for (int64_t m = 0; m < n; ++m) {
-        const int64_t m1 = m / N, m2 = m % N;
-        for (int64_t k = 0; k < n; ++k) {
-          const int64_t l = ((k / N - m1 + N) % N) * N + (k % N - m2 + N) % N;
-          bt[m * n + k] = p->beta[l * n + m];
-        }
-      }
-      for (int j = 0; j < N; ++j) {
-        tw[2 * j] = std::cos(2.0 * kPi * j / N);
-        tw[2 * j + 1] = -std::sin(2.0 * kPi * j / N);
-      }
-      if (!(rc = upload(bt, &p->cl_betaT, p->device_bytes))) rc = upload(tw, &p->cl_tw, p->device_bytes);
+      rc = build_device_classical(p);
     } else if (p->hp.d == 3) {
       rc = build_device_3d(p);
     } else if (fft_supported(p)) {
@@ -843,8 +860,8 @@ static int eval_impl(qcoll_plan_t p, const float* f, void* Q, int64_t cells, cha
     c.q = Q;
     c.cells = cells;
     c.N = p->hp.N;
-    c.betaT = p->cl_betaT;
-    c.tw = p->cl_tw;
+    c.weights = p->cl_weights;
+    c.extra = p->cl_extra;
     c.conserve = (p->flags & QCOLL_CONSERVE) ? 1 : 0;
     for (int i = 0; i < 16; ++i) c.gram_inv[i] = p->hp.gram_inv[i];
     c.L = p->hp.L;

@@ -1,204 +1,253 @@
 // Classical spectral method (section 3.3): Q_hat_k as the direct double sum over
 // l + m = k (modulo N, the collocation reading of the fast method) of
 // beta(l, m) f_hat_l f_hat_m with a dense table of kernel modes, O(N^4) per cell
-// in 2D. FP64 throughout. One workgroup of 256 threads per group of kCb cells:
-// the forward DFT of the group into LDS (two passes of N-point sums), the
-// double sum (each thread owns output modes k = t, t + 256, ... for every cell
-// of the group; the table row betaT[m][.] is read coalesced, f_hat_m is a
-// broadcast and f_hat_{k-m} a gather from LDS), the inverse DFT, and the
-// optional FP64 moment projection.
+// in 2D. FP64 throughout, one launch.
+//
+// Two symmetries leave a quarter of the sum. f is real and beta(-l, -m) =
+// beta(l, m), so Q_hat(-k) is the conjugate of Q_hat(k): rows k1 = 0 .. N/2 are
+// computed. And (l, m), (m, l) multiply the same product: for an output row k1
+// the pairs of rows {m1, k1 - m1} are taken once, with the weight beta(l, m) +
+// beta(m, l) (a row paired with itself keeps its own weights).
+//
+// A workgroup holds C cells in LDS, [mode][cell]; thread (j, c) works on cell c.
+// The transforms are register FFTs (fft_reg.hpp), thread j taking line j. In the
+// sum thread j owns half an output row, N/2 modes (k1, h N/2 + i): row 0 and row
+// N/2 have only their first half, so there are N such tasks (and the two real
+// modes (0, N/2) and (N/2, N/2), summed over all threads). Per pair of rows a
+// thread reads the row l1 into registers once, each f_hat_m once, and runs N x N/2
+// products from registers: 2 N LDS reads for N^2 / 2 products, where reading
+// both factors of every product bound the direct form (about 19 TB/s from LDS).
+//
+// What bounds it: FP64 vector issue, 6 instructions per product (7.1 M wavefront
+// instructions for 4096 cells of 16 x 16, 15 us; one wavefront per SIMD, so LDS and
+// L2 latencies add). 4096 cells of 16 x 16: 35 us (180 for the direct form over all
+// modes and both orders), 16384: 98 (640); 4096 of 24 x 24: 155 (960); 1 cell of 16 x
+// 16: 31 (89).
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
 #include "classical_args.hpp"
+#include "fft_reg.hpp"
 #include "kernels_common.hpp"
 
 namespace qcoll {
 namespace {
 
-constexpr int kCb = 4;          // cells per workgroup
-constexpr int kMaxOut = 3;      // output modes per thread (n <= 768)
+// From this many cells on, workgroups of 16 cells (8 above 20 points, whose 16 would
+// exceed the registers) fill the chip; below, 4 cells, for more workgroups. 16 x 16:
+// 2000 cells 35 us with 4; 4096 cells 38 us with 4, 35 with 16.
+constexpr int64_t kClassicalWide = 4096;
 
-// 16-byte aligned, so that a lane's complex value is one 128-bit LDS access
-// (two 8-byte halves with a 16-byte lane stride conflict in the LDS banks)
-struct alignas(16) cplx {
-  double re, im;
+template <int N, int C>
+struct Classical {
+  static constexpr int n = N * N, H = N / 2, P = N / 2 + 1;   // P pairs of rows per output row
+  static constexpr int W = classical_row(N);                  // doubles per weight row (N/2, even)
+  static constexpr int kThreads = N * C;
+  static constexpr int kLdsBytes = n * C * 16 + 2 * N * C * 8;
 };
 
-__global__ __launch_bounds__(256) void classical_kernel(ClassicalArgs a) {
-  extern __shared__ double2 sh[];   // 16-byte aligned base
-  const int N = a.N, n = N * N;
-  cplx* fh = reinterpret_cast<cplx*>(sh);          // [kCb][n]
-  cplx* tmp = fh + kCb * n;                         // [kCb][n]
-  __shared__ double red[4][4];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  for (int64_t c0 = static_cast<int64_t>(blockIdx.x) * kCb; c0 < a.cells;
-       c0 += static_cast<int64_t>(gridDim.x) * kCb) {
-    const int nc = a.cells - c0 < kCb ? static_cast<int>(a.cells - c0) : kCb;
-    // forward DFT along the last axis: tmp[c][j1][k2] = sum_j2 f[c][j1][j2] w^(k2 j2)
-    for (int i = t; i < kCb * n; i += blockDim.x) {
-      const int c = i / n, r = i - c * n, j1 = r / N, k2 = r - j1 * N;
-      cplx s = {0.0, 0.0};
-      if (c < nc) {
-        const float* fr = a.f + (c0 + c) * n + j1 * N;
-        for (int j2 = 0; j2 < N; ++j2) {
-          const int e = (k2 * j2) % N;
-          const double v = static_cast<double>(fr[j2]);
-          s.re += v * a.tw[2 * e];
-          s.im += v * a.tw[2 * e + 1];
+template <int N, int C>
+__global__ __launch_bounds__(N* C) void classical_kernel(ClassicalArgs a) {
+  using K = Classical<N, C>;
+  constexpr int n = K::n, H = K::H;
+  extern __shared__ double2 A[];                           // [mode][cell]
+  double* part = reinterpret_cast<double*>(A + n * C);     // [2][N][C]
+  const int c = threadIdx.x % C, j = threadIdx.x / C;
+  const int k1 = (j + 1) / 2, h = j == 0 || j == N - 1 ? 0 : (j + 1) & 1;   // this thread's half row
+  for (int64_t c0 = static_cast<int64_t>(blockIdx.x) * C; c0 < a.cells; c0 += static_cast<int64_t>(gridDim.x) * C) {
+    const bool live = c0 + c < a.cells;
+    const int64_t base = (live ? c0 + c : c0) * n;
+    double xr[N], xi[N];
+    // ---- forward: row j along the last axis, then column j along the first, normalised
+#pragma unroll
+    for (int v = 0; v < N; ++v) {
+      xr[v] = static_cast<double>(a.f[base + j * N + v]);
+      xi[v] = 0.0;
+    }
+    dft<N, -1>(xr, xi);
+#pragma unroll
+    for (int v = 0; v < N; ++v) A[(j * N + v) * C + c] = make_double2(xr[v], xi[v]);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < N; ++v) {
+      const double2 z = A[(v * N + j) * C + c];
+      xr[v] = z.x;
+      xi[v] = z.y;
+    }
+    dft<N, -1>(xr, xi);
+#pragma unroll
+    for (int v = 0; v < N; ++v) A[(v * N + j) * C + c] = make_double2(xr[v] * (1.0 / n), xi[v] * (1.0 / n));
+    __syncthreads();
+    // ---- the double sum
+    double ar[H], ai[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) ar[i] = ai[i] = 0.0;
+    const double* wt = a.weights + static_cast<int64_t>(j) * (K::P * N * K::W);
+    int m1 = (k1 + 1) / 2;
+#pragma unroll 1
+    for (int p = 0; p < K::P; ++p) {
+      const int l1 = k1 - m1 < 0 ? k1 - m1 + N : k1 - m1;
+      // row l1 rotated by h N/2: register i holds mode l2 = i + h N/2
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int l2 = (i + h * H) % N;
+        const double2 z = A[(l1 * N + l2) * C + c];
+        xr[i] = z.x;
+        xi[i] = z.y;
+      }
+      const double2* mrow = A + m1 * N * C + c;
+      static_for<N>([&](auto M2) {
+        constexpr int m2 = M2;
+        const double2 fm = mrow[m2 * C];
+        double wv[K::W];
+#pragma unroll
+        for (int i = 0; i < K::W; i += 2) {
+          const double2 w2 = *reinterpret_cast<const double2*>(wt + m2 * K::W + i);
+          wv[i] = w2.x;
+          wv[i + 1] = w2.y;
         }
-      }
-      tmp[i] = s;
+        static_for<H>([&](auto I) {
+          constexpr int i = I, l = (i - m2 + N) % N;   // mode k2 = i + h N/2, l2 = k2 - m2
+          const double ur = wv[i] * fm.x, ui = wv[i] * fm.y;
+          ar[i] = fma(xr[l], ur, fma(-xi[l], ui, ar[i]));
+          ai[i] = fma(xr[l], ui, fma(xi[l], ur, ai[i]));
+        });
+      });
+      wt += N * K::W;
+      m1 = m1 + 1 == N ? 0 : m1 + 1;
     }
-    __syncthreads();
-    // along the first axis, normalised: fh[c][k1][k2] = N^-2 sum_j1 tmp[c][j1][k2] w^(k1 j1)
-    const double inv_n = 1.0 / n;
-    for (int i = t; i < kCb * n; i += blockDim.x) {
-      const int c = i / n, r = i - c * n, k1 = r / N, k2 = r - k1 * N;
-      cplx s = {0.0, 0.0};
-      for (int j1 = 0; j1 < N; ++j1) {
-        const int e = (k1 * j1) % N;
-        const cplx x = tmp[c * n + j1 * N + k2];
-        const double wr = a.tw[2 * e], wi = a.tw[2 * e + 1];
-        s.re += x.re * wr - x.im * wi;
-        s.im += x.re * wi + x.im * wr;
-      }
-      fh[i] = {s.re * inv_n, s.im * inv_n};
-    }
-    __syncthreads();
-    // the double sum
-    cplx acc[kMaxOut][kCb];
-    int k1s[kMaxOut], k2s[kMaxOut];
+    // the real modes (0, N/2) and (N/2, N/2): thread j sums over m1 = j
 #pragma unroll
-    for (int r = 0; r < kMaxOut; ++r) {
-      const int k = t + 256 * r;
-      k1s[r] = k / N;
-      k2s[r] = k - (k / N) * N;
-#pragma unroll
-      for (int c = 0; c < kCb; ++c) acc[r][c] = {0.0, 0.0};
-    }
-    for (int m = 0; m < n; ++m) {
-      const int m1 = m / N, m2 = m - m1 * N;
-      cplx fm[kCb];
-#pragma unroll
-      for (int c = 0; c < kCb; ++c) fm[c] = fh[c * n + m];
-      const double* brow = a.betaT + static_cast<int64_t>(m) * n;
-#pragma unroll
-      for (int r = 0; r < kMaxOut; ++r) {
-        const int k = t + 256 * r;
-        if (k < n) {
-          int l1 = k1s[r] - m1, l2 = k2s[r] - m2;
-          l1 += l1 < 0 ? N : 0;
-          l2 += l2 < 0 ? N : 0;
-          const int l = l1 * N + l2;
-          const double b = brow[k];
-#pragma unroll
-          for (int c = 0; c < kCb; ++c) {
-            const cplx fl = fh[c * n + l];
-            const double pr = fl.re * fm[c].re - fl.im * fm[c].im;
-            const double pi = fl.re * fm[c].im + fl.im * fm[c].re;
-            acc[r][c].re += b * pr;
-            acc[r][c].im += b * pi;
-          }
-        }
-      }
-    }
-    __syncthreads();  // every thread is done with fh: Q_hat goes into tmp
-#pragma unroll
-    for (int r = 0; r < kMaxOut; ++r) {
-      const int k = t + 256 * r;
-      if (k < n)
-#pragma unroll
-        for (int c = 0; c < kCb; ++c) tmp[c * n + k] = acc[r][c];
-    }
-    __syncthreads();
-    // inverse DFT along the first axis: fh[c][j1][k2] = sum_k1 Qh[c][k1][k2] w^(-k1 j1)
-    for (int i = t; i < kCb * n; i += blockDim.x) {
-      const int c = i / n, r = i - c * n, j1 = r / N, k2 = r - j1 * N;
-      cplx s = {0.0, 0.0};
-      for (int k1 = 0; k1 < N; ++k1) {
-        const int e = (k1 * j1) % N;
-        const cplx x = tmp[c * n + k1 * N + k2];
-        const double wr = a.tw[2 * e], wi = -a.tw[2 * e + 1];
-        s.re += x.re * wr - x.im * wi;
-        s.im += x.re * wi + x.im * wr;
-      }
-      fh[i] = s;
-    }
-    __syncthreads();
-    // along the last axis (real part), moments for the projection
-    double* qv = reinterpret_cast<double*>(tmp);   // [kCb][n] real Q
-    for (int i = t; i < kCb * n; i += blockDim.x) {
-      const int c = i / n, r = i - c * n, j1 = r / N, j2 = r - j1 * N;
+    for (int e = 0; e < 2; ++e) {
+      const int l1 = ((e ? H : 0) - j + N) % N;
+      const double* wx = a.extra + (e * N + j) * N;
       double s = 0.0;
-      for (int k2 = 0; k2 < N; ++k2) {
-        const int e = (k2 * j2) % N;
-        const cplx x = fh[c * n + j1 * N + k2];
-        s += x.re * a.tw[2 * e] + x.im * a.tw[2 * e + 1];   // Re(x conj(w^(k2 j2)))
+#pragma unroll
+      for (int m2 = 0; m2 < N; ++m2) {
+        const double2 fm = A[(j * N + m2) * C + c], fl = A[(l1 * N + (H - m2 + N) % N) * C + c];
+        s = fma(wx[m2], fma(fl.x, fm.x, -(fl.y * fm.y)), s);
       }
-      qv[i] = s;
+      part[(e * N + j) * C + c] = s;
+    }
+    __syncthreads();   // the spectrum has been read: Q_hat takes its place
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int k2 = h * H + i;
+      A[(k1 * N + k2) * C + c] = make_double2(ar[i], ai[i]);
+      // rows 0 and N/2: the mirrored half
+      if ((j == 0 || j == N - 1) && i > 0) A[(k1 * N + N - i) * C + c] = make_double2(ar[i], -ai[i]);
+    }
+    if (j < 2) {
+      double s = 0.0;
+#pragma unroll
+      for (int v = 0; v < N; ++v) s += part[(j * N + v) * C + c];
+      A[((j ? H : 0) * N + H) * C + c] = make_double2(s, 0.0);
     }
     __syncthreads();
-    for (int c = 0; c < nc; ++c) {
-      const int64_t base = (c0 + c) * n;
-      if (!a.conserve) {
-        float* Qo = reinterpret_cast<float*>(a.q) + base;
-        for (int i = t; i < n; i += blockDim.x) Qo[i] = static_cast<float>(qv[c * n + i]);
-        continue;
-      }
-      double mm[4] = {0, 0, 0, 0};
-      for (int i = t; i < n; i += blockDim.x) {
-        const int j1 = i / N, j2 = i - j1 * N;
-        const double v1 = -a.L + a.dv * j1, v2 = -a.L + a.dv * j2, q = qv[c * n + i];
-        mm[0] += q;
-        mm[1] += v1 * q;
-        mm[2] += v2 * q;
-        mm[3] += (v1 * v1 + v2 * v2) * q;
-      }
+    // ---- inverse: column j along the first axis (rows k1 > N/2 are conjugates), then row j
 #pragma unroll
-      for (int i = 0; i < 4; ++i) mm[i] = wave_sum(mm[i]);
-      if (lane == 0)
-        for (int i = 0; i < 4; ++i) red[w][i] = mm[i];
+    for (int v = 0; v < N; ++v) {
+      const double2 z = v <= H ? A[(v * N + j) * C + c] : A[((N - v) * N + (j == 0 ? 0 : N - j)) * C + c];
+      xr[v] = z.x;
+      xi[v] = v <= H ? z.y : -z.y;
+    }
+    dft<N, 1>(xr, xi);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < N; ++v) A[(v * N + j) * C + c] = make_double2(xr[v], xi[v]);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < N; ++v) {
+      const double2 z = A[(j * N + v) * C + c];
+      xr[v] = z.x;
+      xi[v] = z.y;
+    }
+    dft<N, 1>(xr, xi);
+    if (!a.conserve) {
+      if (live) {
+        float* Qo = reinterpret_cast<float*>(a.q) + base + j * N;
+#pragma unroll
+        for (int v = 0; v < N; ++v) Qo[v] = static_cast<float>(xr[v]);
+      }
+    } else {   // FP64 projection: moments over the cell's N threads
+      const double v1 = -a.L + a.dv * j;
+      double m[4] = {0, 0, 0, 0};
+#pragma unroll
+      for (int v = 0; v < N; ++v) {
+        const double v2 = -a.L + a.dv * v;
+        m[0] += xr[v];
+        m[2] += v2 * xr[v];
+        m[3] += (v1 * v1 + v2 * v2) * xr[v];
+      }
+      m[1] = v1 * m[0];
+      __syncthreads();   // A is free
+      double* red = reinterpret_cast<double*>(A);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) red[(i * N + j) * C + c] = m[i];
       __syncthreads();
-      double lam[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        lam[i] = 0.0;
+        m[i] = 0.0;
+        for (int v = 0; v < N; ++v) m[i] += red[(i * N + v) * C + c];
+      }
+      double lam[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          lam[i] += a.gram_inv[i * 4 + j] * (red[0][j] + red[1][j] + red[2][j] + red[3][j]);
+      for (int i = 0; i < 4; ++i)
+        lam[i] = a.gram_inv[i * 4 + 0] * m[0] + a.gram_inv[i * 4 + 1] * m[1] + a.gram_inv[i * 4 + 2] * m[2] +
+                 a.gram_inv[i * 4 + 3] * m[3];
+      if (live) {
+        double* Qo = reinterpret_cast<double*>(a.q) + base + j * N;
+#pragma unroll
+        for (int v = 0; v < N; ++v) {
+          const double v2 = -a.L + a.dv * v;
+          Qo[v] = xr[v] - (lam[0] + lam[1] * v1 + lam[2] * v2 + lam[3] * (v1 * v1 + v2 * v2));
+        }
       }
-      double* Qo = reinterpret_cast<double*>(a.q) + base;
-      for (int i = t; i < n; i += blockDim.x) {
-        const int j1 = i / N, j2 = i - j1 * N;
-        const double v1 = -a.L + a.dv * j1, v2 = -a.L + a.dv * j2;
-        Qo[i] = qv[c * n + i] - (lam[0] + lam[1] * v1 + lam[2] * v2 + lam[3] * (v1 * v1 + v2 * v2));
-      }
-      __syncthreads();  // red is reused by the next cell
     }
-    __syncthreads();    // tmp and fh are reused by the next group
+    __syncthreads();   // the next group rewrites A
   }
+}
+
+template <int N, int C>
+int launch_nc(const ClassicalArgs& args, hipStream_t stream) {
+  constexpr int kLds = Classical<N, C>::kLdsBytes;
+  static_assert(kLds <= 160 * 1024, "LDS of a CU");
+  if (kLds > 64 * 1024) {   // above the default limit of dynamic LDS
+    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(classical_kernel<N, C>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, kLds) == hipSuccess;
+    if (!ok) return -3;
+  }
+  const int64_t groups = (args.cells + C - 1) / C;
+  const int64_t blocks = groups < 4096 ? groups : 4096;
+  hipLaunchKernelGGL((classical_kernel<N, C>), dim3(static_cast<unsigned>(blocks)), dim3(N * C), kLds, stream, args);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+template <int N>
+int launch_n(const ClassicalArgs& args, hipStream_t stream) {
+  return args.cells >= kClassicalWide ? launch_nc<N, (N > 20 ? 8 : 16)>(args, stream) : launch_nc<N, 4>(args, stream);
 }
 
 }  // namespace
 
 int launch_classical(const ClassicalArgs& args, hipStream_t stream) {
   if (args.cells <= 0) return 0;
-  const int n = args.N * args.N;
-  if (n > 256 * kMaxOut) return -1;
-  const unsigned lds = static_cast<unsigned>(2 * kCb * n * sizeof(double) * 2);
-  // up to 2 x kCb x 768 complex doubles = 96 KiB (n <= 768)
-  static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(classical_kernel),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                  static_cast<int>(2 * kCb * 256 * kMaxOut * sizeof(double) * 2)) ==
-                              hipSuccess;
-  if (!attr_ok) return -3;
-  const int64_t groups = (args.cells + kCb - 1) / kCb;
-  const int64_t blocks = groups < 4096 ? groups : 4096;
-  hipLaunchKernelGGL(classical_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, stream, args);
-  return hipGetLastError() == hipSuccess ? 0 : -3;
+  switch (args.N) {
+    case 4: return launch_n<4>(args, stream);
+    case 6: return launch_n<6>(args, stream);
+    case 8: return launch_n<8>(args, stream);
+    case 10: return launch_n<10>(args, stream);
+    case 12: return launch_n<12>(args, stream);
+    case 14: return launch_n<14>(args, stream);
+    case 16: return launch_n<16>(args, stream);
+    case 18: return launch_n<18>(args, stream);
+    case 20: return launch_n<20>(args, stream);
+    case 22: return launch_n<22>(args, stream);
+    case 24: return launch_n<24>(args, stream);
+    default: return -1;
+  }
 }
 
 }  // namespace qcoll

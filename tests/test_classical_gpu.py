@@ -116,3 +116,29 @@ def test_vhs_fast_parity(qc, gamma, precision, N):
     print(f"vhs gamma={gamma} {precision} N={N}: rel L2 {err:.3e}")
     assert err < (1e-5 if precision == "fx16" else 2e-4)
     plan.close()
+
+
+@pytest.mark.parametrize("N", range(4, 25, 2))
+def test_classical_every_grid_size(N):
+    """The direct sum over half the output modes and unordered pairs, on every grid
+    size (odd N/2 has padded weight rows) and both workgroup widths, against the FP64
+    oracle of the same separable modes. Tolerance: sums of N^2 products of relative
+    rounding 1e-16 each, times the gain's norm; 1e-12 of it leaves a factor of more
+    than 10 for the tables, which the two sides build separately."""
+    L = 3.0 + 0.2 * N
+    s = sp.Setup(d=2, N=N, L=L, kernel="hard_sphere", M=6)
+    f = wl.mixture_cells(2, N, L, 5, 70 + N).astype(np.float32)
+    f *= np.linspace(0.5, 2.0, 5, dtype=np.float32)[:, None, None]
+    q, gain, _ = sp.q_fast(f.astype(np.float64), s, return_parts=True)
+    ref = sp.project_conservative(q, 2, L)
+    from paper_2103_14890_amd import qcoll
+    plan = qcoll.Plan(2, N, L, "hard_sphere", 6, classical=True, separable_modes=True, conserve=True)
+    t = torch.tensor(f, device="cuda:0")
+    got = plan.eval(t).cpu().numpy()
+    assert np.linalg.norm(got - ref) <= 1e-12 * np.linalg.norm(gain)
+    cells = 4099   # wide workgroups, the last one ragged
+    wide = plan.eval(t.repeat(820, 1, 1)[:cells].contiguous()).cpu().numpy()
+    ref_wide = np.tile(ref, (820, 1, 1))[:cells]
+    worst = np.abs(wide - ref_wide).reshape(cells, -1).max(axis=1)
+    assert worst.max() <= 1e-12 * np.linalg.norm(gain)
+    plan.close()
