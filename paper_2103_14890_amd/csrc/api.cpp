@@ -637,6 +637,7 @@ qcoll::KernelArgs make_args(const qcoll_plan_s* p) {
   a.dv = 2.0 * p->hp.L / p->hp.N;
   a.max_blocks = p->max_blocks;
   a.waves_per_block = p->waves_per_block;
+  a.round_cells = p->cus;   // (one workgroup per CU: 256 cells 62 -> 31 us, a second round of workgroups would gain little)
   a.tile = p->tile;
   a.fft = p->fft ? 1 : 0;
   a.tw = p->tw;

@@ -343,6 +343,134 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
   }
 }
 
+// ------------------------------------------------------------ FX16, few cells
+//
+// The same computation with the eight wavefronts of a workgroup on one cell, for
+// batches that leave most of the chip idle (a lone cell runs its transforms one
+// after another otherwise). The transforms go in rounds of eight, one per wavefront;
+// each leaves its two fields in LDS, and then every wavefront adds the round's
+// products, in the order of the transforms, at two of the sixteen registers' points.
+// The order of every sum is that of fx16_t32_body, so the results are bitwise equal.
+// One 32 x 32 cell (hard spheres, M = 8, projection): 59 -> 27 us, 256 cells 62 -> 31.
+constexpr int kRoundLdsBytes = kEoLdsBytes + 9 * kFhatLdsBytes;   // table, spectrum, eight fields
+
+template <int OUT>
+__device__ __forceinline__ void fx16_t32_round_body(const KernelArgs& a, int64_t first, int64_t stride, double2* fh,
+                                                    const half8* eo) {
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double2* fields = fh + kFhatLdsBytes / 16;   // [transform of the round][register][lane]
+  Lead E[3][2];
+  {
+    const half8* src = reinterpret_cast<const half8*>(a.econst) + lane * 18;
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) E[m][s].l = src[(m * 2 + s) * 3 + 0];
+  }
+  for (int64_t cell = first; cell < a.cells; cell += stride) {
+    f32x16 r0{}, r1{}, i0{}, i1{};
+    Split3 A[4];
+    int s_fh;
+    // forward transform, by every wavefront; wavefront 0 stores the spectrum
+    {
+      float fv[16];
+      load_cell<Lay32>(a, cell, lane, fv);
+      float fm = 0.0f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) fm = fmaxf(fm, fabsf(fv[v]));
+      fm = wave_max(fm);
+      const int a0 = 9 - exp_above(fm);
+      const double cf = ldexp(1.0, a0);
+#pragma unroll
+      for (int v = 0; v < 16; v += 2)
+        put2(A[v >> 3], v & 7, split2_f64(static_cast<double>(fv[v]) * cf, static_cast<double>(fv[v + 1]) * cf));
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        mma6_lo_lds(A[s], E[kEr][s], eo + (kEr * 2 + s) * 64 + lane, r0, r1);
+        mma6_lo_lds(A[s], E[kNEi][s], eo + (kNEi * 2 + s) * 64 + lane, i0, i1);
+      }
+      s_fh = -(a0 + 9);
+    }
+    {
+      const int a1 = 9 - exp_above(tile_absmax(r0, r1, i0, i1));
+      slice_tiles(r0, r1, i0, i1, ldexpf(1.0f, a1), A);
+      pass64_lo_lds(A, E, eo, kEr, kEi, kNEi, kEr, true, r0, r1, i0, i1);
+      s_fh -= a1 + 9;
+    }
+    {
+      float fhm = 0.0f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        fhm = fmaxf(fhm, fmaxf(fabsf(r0[v] + r1[v]), fabsf(i0[v] + i1[v])));
+      fhm = wave_max(fhm * 1.0000002f);
+      const int bsh = 9 - (exp_above(fhm) + 1);
+      if (wv == 0) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          fh[v * 64 + lane] = make_double2(ldexp(static_cast<double>(r0[v]) + static_cast<double>(r1[v]), bsh),
+                                           ldexp(static_cast<double>(i0[v]) + static_cast<double>(i1[v]), bsh));
+      }
+      s_fh -= bsh;
+    }
+    __syncthreads();
+    double gain[2] = {0.0, 0.0};   // at registers 2 wv and 2 wv + 1
+    float fl[2];                   // f there, for the loss term
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r = Lay32::row(2 * wv + j, lane), c = Lay32::col(lane);
+      fl[j] = load_or_zero(a.f + cell * static_cast<int64_t>(a.n) * a.n, r < a.n && c < a.n, r * a.n + c);
+    }
+    for (int q0 = 0; q0 <= a.P; q0 += 8) {
+      const int q = q0 + wv;
+      if (q <= a.P) {   // wavefront-uniform
+        double2 mv[16];
+        const unsigned l16 = opaque_lane16(lane);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mv[v] = load_filter_value(a.filt, q, v, l16);
+        filtered_split(mv, fh, lane, A);
+        pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, true, r0, r1, i0, i1);
+        const int a2 = 9 - exp_above(tile_absmax(r0, r1, i0, i1));
+        slice_tiles(r0, r1, i0, i1, ldexpf(1.0f, a2), A);
+        pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, true, r0, r1, i0, i1);
+        const int sd = a.filt_exp[q] + s_fh - 9 - a2 - 9;
+        double2* mine = fields + wv * (kFhatLdsBytes / 16);
+        const double w = ldexp(1.0, 2 * sd);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const double re = static_cast<double>(r0[v]) + static_cast<double>(r1[v]);
+          const double im = static_cast<double>(i0[v]) + static_cast<double>(i1[v]);
+          mine[v * 64 + lane] = q < a.P ? make_double2(re * w, im) : make_double2(ldexp(re, sd), 0.0);
+        }
+      }
+      __syncthreads();
+      const int n = a.P + 1 - q0 < 8 ? a.P + 1 - q0 : 8;
+      for (int k = 0; k < n; ++k) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const double2 z = fields[k * (kFhatLdsBytes / 16) + (2 * wv + j) * 64 + lane];
+          if (q0 + k < a.P) gain[j] = fma(z.x, z.y, gain[j]);
+          else gain[j] = gain[j] - static_cast<double>(fl[j]) * z.x;   // the loss: Q = gain - f L
+        }
+      }
+      __syncthreads();
+    }
+    double* all = reinterpret_cast<double*>(fields);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) all[(2 * wv + j) * 64 + lane] = gain[j];
+    __syncthreads();
+    if (wv == 0) {
+      double Q[16];
+      float fv[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) Q[v] = all[v * 64 + lane];
+      load_cell<Lay32>(a, cell, lane, fv, static_cast<float>(Q[0]));
+      finish_cell<OUT, Lay32>(a, cell, fv, Q, lane);
+    }
+    __syncthreads();   // spectrum and fields are rewritten by the next cell
+  }
+}
+
 // ------------------------------------------------------------ FX16 ping-pong
 //
 // The same computation with eight wavefronts per workgroup, two per SIMD, run

@@ -51,6 +51,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
                      lds + (kEoLdsBytes + w * kFhatLdsBytes) / 16, eo);
 }
 
+// Few cells: eight wavefronts per cell (fx16_t32_round_body).
+template <int OUT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void fx16_t32_round_kernel(KernelArgs a) {
+  extern __shared__ double2 lds[];
+  half8* eo = reinterpret_cast<half8*>(lds);
+  load_eo_table(a, eo);
+  fx16_t32_round_body<OUT>(a, blockIdx.x, gridDim.x, lds + kEoLdsBytes / 16, eo);
+}
+
+template <int OUT>
+int launch_round(const KernelArgs& args, hipStream_t stream) {
+  static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_round_kernel<OUT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kRoundLdsBytes) == hipSuccess;
+  if (!ok) return -3;
+  hipLaunchKernelGGL(fx16_t32_round_kernel<OUT>, dim3(static_cast<unsigned>(args.cells)), dim3(512), kRoundLdsBytes,
+                     stream, args);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
 // Ping-pong variant: eight wavefronts (two per SIMD) in alternating phases.
 // The two wavefronts that share a SIMD take opposite roles: each wavefront
 // reads its SIMD from the hardware-ID register, and the second of the
@@ -85,6 +104,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 int launch_2d32(const KernelArgs& args, hipStream_t stream) {
   if (args.cells <= 0) return 0;
   const int wpb = args.waves_per_block;
+  if (args.precision == 4 && args.cells <= args.round_cells) {
+    switch (args.out_kind) {
+      case 0: return launch_round<0>(args, stream);
+      case 1: return launch_round<1>(args, stream);
+      case 2: return launch_round<2>(args, stream);
+      case 3: return launch_round<3>(args, stream);
+      default: return launch_round<4>(args, stream);
+    }
+  }
   int64_t blocks = (args.cells + wpb - 1) / wpb;
   if (blocks > args.max_blocks) blocks = args.max_blocks;
   dim3 grid(static_cast<unsigned>(blocks)), block(64 * wpb);

@@ -286,3 +286,31 @@ def test_calls_on_a_side_stream_with_library_allocated_buffers(qc):
     assert torch.equal(f, ref_f)
     del junk
     plan.close()
+
+
+@pytest.mark.parametrize("N,kernel,M", [(32, "hard_sphere", 8), (18, "hard_sphere", 6), (32, "maxwell", 14),
+                                        (26, "maxwell", 16), (32, "maxwell", 2)])
+def test_few_cells_equal_the_full_batch_bitwise(qc, N, kernel, M):
+    """Few cells run eight wavefronts per cell in rounds of eight transforms (here 21
+    or more, 8, 9 and 2 entries with the loss): bitwise the results of the same cells
+    in a batch that runs one wavefront per cell, for every output of such plans."""
+    cells = 600
+    f0 = torch.tensor(wl.mixture_cells(2, N, 8.0, cells, 60 + N), dtype=torch.float32, device="cuda")
+    plan = qc.Plan(2, N, 8.0, kernel, M, precision="fx16", conserve=True)
+
+    def outputs(f):
+        fe, fr = f.clone(), f.clone()
+        st = torch.full((f.shape[0],), -1, dtype=torch.int32, device="cuda")
+        plan.step(fe, 0.02, 0.5, "imex", st)
+        plan.step_rk(fr, 0.02, 0.5, "bpr343")
+        return [plan.eval(f), fe, fr, st]
+
+    full = outputs(f0)
+    for lo, hi in ((0, 1), (5, 14), (17, 17 + 256)):
+        for a, b in zip(outputs(f0[lo:hi].contiguous()), full):
+            assert torch.equal(a, b[lo:hi])
+    plan.close()
+    gal = qc.Plan(2, 16, 8.0, kernel, M, precision="fx16", galerkin=True)   # fine grid of 24 points
+    g0 = torch.tensor(wl.mixture_cells(2, 16, 8.0, cells, 61), dtype=torch.float32, device="cuda")
+    assert torch.equal(gal.eval_galerkin(g0[3:20].contiguous()), gal.eval_galerkin(g0)[3:20])
+    gal.close()
