@@ -231,9 +231,9 @@ int qcoll_step_rk_noalloc(qcoll_plan_t plan, float* f, int64_t cells, double dt,
  * (or status[i]) and cells[i] exactly as the single-plan call; each cell's
  * result is bitwise equal to the single-plan launch. nplans <= 64, all plans
  * on one device; slots with cells[i] == 0 are skipped. status may be NULL.
- * 2D plans share one launch per 8 slots (N <= 32: a wavefront per cell; N > 32:
+ * 2D plans share one launch per 16 slots (N <= 32: a wavefront per cell; N > 32:
  * a workgroup per cell); 3D plans (all slots 3D) share one launch per 8 slots.
- * When a 2D call has several launches (more than 8 slots) and few cells (at
+ * When a 2D call has several launches (more than 16 slots) and few cells (at
  * most four per compute unit in total, as in a serving tick) they run
  * concurrently, the first on `stream` and the others on up to three side
  * streams of the library (default priority) that wait for `stream` before

@@ -35,8 +35,7 @@ struct qcoll_plan_s {
   void* econst = nullptr;
   double* filt = nullptr;
   int* filt_exp = nullptr;
-  double* loss = nullptr;
-  int loss_exp = 0;
+  double* gram = nullptr;   // inverse Gram matrix of the projection (2D fast plans)
   float* filt32 = nullptr;
   float* loss32 = nullptr;
   double* tw = nullptr;
@@ -106,7 +105,7 @@ void free_device(qcoll_plan_s* p) {
   hipFree(p->econst);
   hipFree(p->filt);
   hipFree(p->filt_exp);
-  hipFree(p->loss);
+  hipFree(p->gram);
   hipFree(p->filt32);
   hipFree(p->loss32);
   hipFree(p->tw);
@@ -128,7 +127,7 @@ void free_device(qcoll_plan_s* p) {
   p->scratch = nullptr;
   p->tw = nullptr;
   p->econst = nullptr;
-  p->filt = p->loss = nullptr;
+  p->filt = p->gram = nullptr;
   p->filt_exp = nullptr;
   p->filt32 = p->loss32 = nullptr;
 }
@@ -626,12 +625,10 @@ qcoll::KernelArgs make_args(const qcoll_plan_s* p) {
   a.econst = p->econst;
   a.filt = p->filt;
   a.filt_exp = p->filt_exp;
-  a.loss = p->loss;
-  a.loss_exp = p->loss_exp;
   a.filt32 = p->filt32;
   a.loss32 = p->loss32;
   a.P = static_cast<int>(p->hp.packed.size());
-  for (int i = 0; i < 16 && i < static_cast<int>(p->hp.gram_inv.size()); ++i) a.gram_inv[i] = p->hp.gram_inv[i];
+  a.gram_inv = p->gram;
   a.n = p->hp.N;
   a.L = p->hp.L;
   a.dv = 2.0 * p->hp.L / p->hp.N;
@@ -805,6 +802,7 @@ static int plan_create(qcoll_plan_t* out, int d, int n_per_dim, double L, int ke
         swap_tile_tables(p);
       }
     }
+    if (!rc && p->hp.d == 2 && !p->classical) rc = upload(p->hp.gram_inv, &p->gram, p->device_bytes);
     if (!rc && p->galerkin) {
       std::vector<double> gi, gr;
       qcoll::galerkin_operators(p->hp_coarse.N, p->hp.N, gi, gr);
@@ -1102,7 +1100,7 @@ static ForkJoin* fork_join(int dev) {
   return &pool[dev];
 }
 
-// One launch of a batched 2D call: a slot table of up to kMaxSlots plans (N <= 32
+// One launch of a batched 2D call: a slot table of up to kMaxSlots2 plans (N <= 32
 // tiles, a wavefront per cell; tile-64 plans, a workgroup per cell).
 struct MultiJob {
   qcoll::MultiArgs m;
@@ -1291,7 +1289,7 @@ static int multi_launch(const qcoll_plan_t* plans, int nplans, const float* cons
       a.q = Q[i];
       a.out_kind = (p->flags & QCOLL_CONSERVE) ? 1 : 0;
     }
-    if (m.nslots == qcoll::kMaxSlots) {  // slot table full: queue it and start the next
+    if (m.nslots == qcoll::kMaxSlots2) {  // slot table full: queue it and start the next
       m.block_start[m.nslots] = blocks;
       jobs.emplace_back();
       jobs.back().m = m;

@@ -16,13 +16,11 @@ struct KernelArgs {
   const double* filt = nullptr; // FX16 filters: FFT kernels (layout set by the grid); matrix kernels scaled by
                                 // 2^-filt_exp (layout set by the tile family)
   const int* filt_exp = nullptr;
-  const double* loss = nullptr; // FX16: [64 lanes][16 modes], scaled by 2^-loss_exp
-  int loss_exp = 0;
   const double* tw = nullptr;   // tile-64 matrix kernel: w^(k p), [p in {0,1}][k < 32][re, im]; FFT: w^(i j), [4][16][re, im]
   const float* filt32 = nullptr;  // FP32: [P][64][16][re, im]
   const float* loss32 = nullptr;  // FP32: [64][16]
   int P = 0;                    // packed gain transforms
-  double gram_inv[16] = {};     // inverse Gram matrix of (1, v1, v2, |v|^2), row-major
+  const double* gram_inv = nullptr;  // device: inverse Gram matrix of (1, v1, v2, |v|^2), row-major [16]
   double L = 0, dv = 0;
   double dt_eps = 0;            // dt / eps
   int scheme = 0;
@@ -61,12 +59,15 @@ struct KernelArgs {
 
 // Batched launch over several plans: slot s owns workgroups
 // [block_start[s], block_start[s+1]) of the grid.
-constexpr int kMaxSlots = 8;
+// (sixteen slots keep the argument block below 4 KB).
+constexpr int kMaxSlots2 = 16;
 struct MultiArgs {
   int nslots = 0;
-  int64_t block_start[kMaxSlots + 1] = {};
-  KernelArgs slot[kMaxSlots];
+  int64_t block_start[kMaxSlots2 + 1] = {};
+  KernelArgs slot[kMaxSlots2];
 };
+static_assert(sizeof(MultiArgs) <= 4096, "kernel argument block");
+constexpr int kMaxSlots = 8;   // slots of a 3D launch
 
 // 3D velocity grids (FP32 MFMA; one workgroup of four wavefronts per cell).
 // Slot s of a launch covers the cells [cell_start[s], cell_start[s+1]) of the

@@ -3,7 +3,7 @@
 // so every cell runs exactly the code of its single-plan launch and the
 // results are bitwise equal to separate launches. Workgroups are assigned to
 // slots by contiguous ranges; a workgroup finds its slot with a short scan of
-// the slot table (at most kMaxSlots entries) and then walks its slot's cells:
+// the slot table (at most kMaxSlots2 entries) and then walks its slot's cells:
 // one cell per wavefront on 16x16 and 32x32 tiles, one cell per workgroup of
 // four wavefronts on the 64-point grids (the tile-64 body).
 

@@ -160,13 +160,18 @@ def _alloc(shape, dtype, like, stream):
     return t
 
 
-def _dev_ptr(t, dtype, name):
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+def _address(t, dtype, name, tensor_type) -> int:
+    """Device address of a checked tensor."""
+    if not isinstance(t, tensor_type) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if t.dtype != dtype or not t.is_contiguous():
         raise TypeError(f"{name} must be a contiguous {dtype} tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _dev_ptr(t, dtype, name):
+    import torch
+    return ctypes.c_void_p(_address(t, dtype, name, torch.Tensor))
 
 
 class Plan:
@@ -390,21 +395,14 @@ class Plan:
             pass
 
 
-def _ptr_array(items):
-    arr = (ctypes.c_void_p * len(items))()
-    for i, it in enumerate(items):
-        arr[i] = it
-    return arr
-
-
 def eval_multi(plans, fs, qs, stream=None):
     """One launch over several plans (qcoll_eval_multi); fs, qs device tensors."""
     import torch
-    n = len(plans)
-    pl = _ptr_array([p._h.value for p in plans])
-    fp = _ptr_array([_dev_ptr(f, torch.float32, "f").value for f in fs])
-    qp = _ptr_array([_dev_ptr(q, torch.float64 if p.conserve else torch.float32, "Q").value
-                     for p, q in zip(plans, qs)])
+    n, T, f32, f64 = len(plans), torch.Tensor, torch.float32, torch.float64
+    vps = ctypes.c_void_p * n
+    pl = vps(*[p._h.value for p in plans])
+    fp = vps(*[_address(f, f32, "f", T) for f in fs])
+    qp = vps(*[_address(q, f64 if p.conserve else f32, "Q", T) for p, q in zip(plans, qs)])
     cells = (ctypes.c_int64 * n)(*[f.shape[0] for f in fs])
     _check(LIB.qcoll_eval_multi(pl, n, fp, qp, cells, _stream_ptr(stream)), "qcoll_eval_multi")
     return qs
@@ -413,13 +411,14 @@ def eval_multi(plans, fs, qs, stream=None):
 def step_multi(plans, fs, dt: float, eps: float = 1.0, scheme: str = "explicit", statuses=None, stream=None):
     """One stage update over several plans in one launch (qcoll_step_multi)."""
     import torch
-    n = len(plans)
-    pl = _ptr_array([p._h.value for p in plans])
-    fp = _ptr_array([_dev_ptr(f, torch.float32, "f").value for f in fs])
+    n, T, f32, i32 = len(plans), torch.Tensor, torch.float32, torch.int32
+    vps = ctypes.c_void_p * n
+    pl = vps(*[p._h.value for p in plans])
+    fp = vps(*[_address(f, f32, "f", T) for f in fs])
     cells = (ctypes.c_int64 * n)(*[f.shape[0] for f in fs])
     st = None
     if statuses is not None:
-        st = _ptr_array([0 if s is None else _dev_ptr(s, torch.int32, "status").value for s in statuses])
+        st = vps(*[0 if s is None else _address(s, i32, "status", T) for s in statuses])
     _check(LIB.qcoll_step_multi(pl, n, fp, cells, float(dt), float(eps), _SCHEMES[scheme], st,
                                 _stream_ptr(stream)), "qcoll_step_multi")
     return fs

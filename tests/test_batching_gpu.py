@@ -314,3 +314,21 @@ def test_few_cells_equal_the_full_batch_bitwise(qc, N, kernel, M):
     g0 = torch.tensor(wl.mixture_cells(2, 16, 8.0, cells, 61), dtype=torch.float32, device="cuda")
     assert torch.equal(gal.eval_galerkin(g0[3:20].contiguous()), gal.eval_galerkin(g0)[3:20])
     gal.close()
+
+
+def test_more_plans_than_a_slot_table(qc):
+    """Forty slots: three slot tables (concurrently on side streams: few cells), every
+    result bitwise that of the single-plan call, twice in a row without a
+    synchronisation in between."""
+    plans, fs = [], []
+    for i in range(40):
+        N = (16, 24, 32, 48, 20)[i % 5]
+        plans.append(qc.Plan(2, N, 8.0, "maxwell" if i % 2 else "hard_sphere", 8, precision="fx16", conserve=i % 7 == 0))
+        fs.append(torch.tensor(wl.mixture_cells(2, N, 8.0, 1 + i % 3, 300 + i), dtype=torch.float32, device="cuda"))
+    qs = [torch.empty(f.shape, dtype=torch.float64 if p.conserve else torch.float32, device="cuda")
+          for p, f in zip(plans, fs)]
+    qc.eval_multi(plans, fs, qs)
+    qc.eval_multi(plans, fs, qs)
+    for p, f, q in zip(plans, fs, qs):
+        assert torch.equal(q, p.eval(f))
+        p.close()
