@@ -20,11 +20,11 @@
 // table and the spectrum hold half of the rows.
 //
 // What bounds it: FP64 vector issue. Per pair of 32-point transforms a lane issues
-// 990 FP64 instructions (2 x 418 FFT, 124 filter, 32 gain), 64 lane swaps and 31
+// 930 FP64 instructions (2 x 387 FFT, 124 filter, 32 gain), 64 lane swaps and 31
 // sign flips, against about 1660 vector instructions and 192 MFMAs of the
-// split-FP16 matrix form. 4096 cells of 32 x 32 (hard spheres, M = 8) take 57.7 M
-// wavefront instructions, 124-135 us at the 2.2-2.4 ns per instruction that two
-// wavefronts on a SIMD reach; measured 145 us, the matrix form 216 us.
+// split-FP16 matrix form. 4096 cells of 32 x 32 (hard spheres, M = 8) take 54.5 M
+// wavefront instructions, 117-128 us at the 2.2-2.4 ns per instruction that two
+// wavefronts on a SIMD reach; measured 140 us, the matrix form 216 us.
 #pragma once
 
 #include "fft_reg.hpp"
