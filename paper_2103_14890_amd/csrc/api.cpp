@@ -344,14 +344,18 @@ int launch(const qcoll::KernelArgs& a, hipStream_t stream) {
 // up to 32 points per axis and of 36, 40, .. 64 (the workgroup kernel splits a line
 // in four). Measured against the split-FP16 matrix kernels (4096 cells, M =
 // 8, hard spheres, float Q): 20 points 195 -> 80 us, 24 points 201 -> 99, 32 points
-// 216 -> 145; 10000 cells of 16 points 101 -> 73 (Maxwell, M = 16: 48.6 -> 45.5);
-// 4000 cells of 48 points 1227 -> 656, of 64 points 1318 -> 962.
+// 216 -> 140; 10000 cells of 16 points 103 -> 68 (Maxwell, M = 16: 50.8 -> 37.1);
+// 4000 cells of 48 points 1227 -> 656, of 64 points 1318 -> 920. On 14 and 16 points a
+// plan of fewer than six packed transforms leaves the four transform slots of a
+// wavefront half idle (1000 cells of 16 points, Maxwell, M = 8: 8.0 -> 8.4 us, 2048:
+// 10.0 -> 11.9) and keeps the matrix kernels.
 // Plans with the projection stay on the matrix kernels: their double Q carries the
 // digits of that arithmetic below 1e-6, and callers compare it with earlier
 // results at double precision. So do the fine grids of Galerkin plans.
 bool fft_supported(const qcoll_plan_s* p) {
   return p->hp.d == 2 && p->precision == QCOLL_MIX_FX16 && !(p->flags & QCOLL_CONSERVE) && !p->galerkin &&
-         (p->hp.N <= 32 || p->hp.N % 4 == 0);
+         (p->hp.N <= 32 || p->hp.N % 4 == 0) &&
+         !(p->hp.N > 12 && p->hp.N <= 16 && p->hp.packed.size() < 6);
 }
 
 // Filter table of the FFT kernels. Entry q < P is the packed multiplier of gain
@@ -634,7 +638,7 @@ qcoll::KernelArgs make_args(const qcoll_plan_s* p) {
   a.dv = 2.0 * p->hp.L / p->hp.N;
   a.max_blocks = p->max_blocks;
   a.waves_per_block = p->waves_per_block;
-  a.round_cells = p->cus;   // (one workgroup per CU: 256 cells 62 -> 31 us, a second round of workgroups would gain little)
+  a.cus = p->cus;
   a.tile = p->tile;
   a.fft = p->fft ? 1 : 0;
   a.tw = p->tw;

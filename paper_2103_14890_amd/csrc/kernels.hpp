@@ -52,7 +52,7 @@ struct KernelArgs {
   int split = 1;
   double* split_ws = nullptr;
   int* split_cnt = nullptr;
-  int64_t round_cells = 0;      // FX16 32x32 tiles: up to so many cells run eight wavefronts per cell
+  int cus = 256;                // compute units (rules on few and many cells)
   int waves_per_block = 4;      // launch shape (1, 2 or 4 wavefronts, one cell each)
   int64_t max_blocks = 1 << 20; // grid cap; waves loop over cells beyond it
 };

@@ -33,6 +33,38 @@ int launch_n(const KernelArgs& args, dim3 grid, dim3 block, hipStream_t stream) 
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
+// Cells 0 .. full - 1 four to a wavefront (the first `blocks` workgroups), the rest
+// one to a wavefront.
+template <int N>
+__global__ __launch_bounds__(256, 2) void fft_cells_kernel(KernelArgs a, int64_t full, int blocks) {
+  extern __shared__ double lds[];
+  const int w = threadIdx.x >> 6;
+  const int b = static_cast<int>(blockIdx.x);
+  double* mine = lds + w * (FftCells<N>::kWaveBytes / 8);
+  if (b < blocks)
+    fft_cells_body<N>(a, static_cast<int64_t>(b) * 4 + w, static_cast<int64_t>(blocks) * 4, full, mine);
+  else
+    fft_body<N, true>(a, full + static_cast<int64_t>(b - blocks) * 4 + w,
+                      static_cast<int64_t>(gridDim.x - blocks) * 4, false, 0, mine);
+}
+
+template <int N>
+int launch_cells(const KernelArgs& args, int64_t full, hipStream_t stream) {
+  static_assert(FftCells<N>::kWaveBytes >= FftGrid<N>::kWaveBytes, "both forms run in one kernel");
+  constexpr int kLds = 4 * FftCells<N>::kWaveBytes;
+  if (kLds > 64 * 1024) {
+    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(fft_cells_kernel<N>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, kLds) == hipSuccess;
+    if (!ok) return -3;
+  }
+  int64_t blocks = (full + 15) / 16, rest = (args.cells - full + 3) / 4;
+  if (blocks > args.max_blocks) blocks = args.max_blocks;
+  if (rest > args.max_blocks) rest = args.max_blocks;
+  hipLaunchKernelGGL(fft_cells_kernel<N>, dim3(static_cast<unsigned>(blocks + rest)), dim3(256), kLds, stream, args,
+                     full, static_cast<int>(blocks));
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
 }  // namespace
 
 int launch_fft(const KernelArgs& args, hipStream_t stream) {
@@ -41,6 +73,31 @@ int launch_fft(const KernelArgs& args, hipStream_t stream) {
   int64_t blocks = (args.cells + wpb - 1) / wpb;
   if (blocks > args.max_blocks) blocks = args.max_blocks;
   const dim3 grid(static_cast<unsigned>(blocks)), block(64 * wpb);
+  // Four cells per wavefront from whole rounds of one such wavefront per SIMD on. What
+  // is left over joins them where it would take longer a cell per wavefront: a round
+  // costs about as much as unit (P + 2) / 5 cells at 1 + G passes each (G groups of four
+  // of the P + 1 transforms) beside other rounds, and half as much again alone, where
+  // those cells get three wavefronts per SIMD. 16 x 16 Maxwell M = 8 (P = 4): 2048 cells
+  // 11.9 us alone and 13 four to a wavefront, 3500 17.8 and 13.3, 7000 23.9 (2904 of
+  // them alone) and 20.5; hard spheres M = 8 (P = 32): 3500 31 and 35, 6000 44 and 56.
+  if (args.n <= 16 && (args.out_kind == 0 || args.out_kind == 2)) {
+    const int64_t unit = 16 * static_cast<int64_t>(args.cus);
+    int64_t full = args.cells / unit * unit;
+    const int64_t G = args.P / 4 + 1;
+    if (10 * (args.cells - full) * (1 + G) >= (full > 0 ? 2 : 3) * unit * (args.P + 2)) full = args.cells;
+    if (full > 0) {
+      switch (args.n) {
+        case 4: return launch_cells<4>(args, full, stream);
+        case 6: return launch_cells<6>(args, full, stream);
+        case 8: return launch_cells<8>(args, full, stream);
+        case 10: return launch_cells<10>(args, full, stream);
+        case 12: return launch_cells<12>(args, full, stream);
+        case 14: return launch_cells<14>(args, full, stream);
+        case 16: return launch_cells<16>(args, full, stream);
+        default: break;
+      }
+    }
+  }
   switch (args.n) {
 #define QCOLL_FFT_LAUNCH(N) \
   case N: return launch_n<N>(args, grid, block, stream);

@@ -57,3 +57,34 @@ def test_every_grid_size(N):
             plan.set_split(split)
             assert _rel(plan.eval(t).cpu().double().numpy(), ref) < 1.5e-7, (N, split)
     plan.close()
+
+
+@pytest.mark.parametrize("N", range(4, 17, 2))
+def test_many_cells_equal_few_bitwise(N):
+    """Four cells per wavefront (whole rounds of 16 cells per compute unit, and what
+    is left over, alone or four to a wavefront) against a cell per wavefront."""
+    f, L, kernel, M, _ = _case(N, 7)
+    plan = qcoll.Plan(2, N, L, kernel, M)
+    few = torch.tensor(f, device=DEV)
+    q = plan.eval(few)
+    g, st = few.clone(), torch.empty(7, dtype=torch.int32, device=DEV)
+    few[5, 1, 1] = float("nan")   # its four-cell neighbours keep status 0
+    bad = few.clone()
+    plan.step(g, 0.01, 1.0, "explicit")
+    plan.step(bad, 0.01, 1.0, "explicit", status=st)
+    assert st.cpu().tolist() == [0] * 5 + [1, 0]
+    unit = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    for cells in (unit - 1, unit, unit + 5, 2 * unit + unit // 2 + 2, 2 * unit + unit - 3):
+        idx = torch.arange(cells, device=DEV) % 7
+        many = torch.tensor(f, device=DEV)[idx].contiguous()
+        assert torch.equal(plan.eval(many), q[idx]), cells
+        status = torch.full((cells,), -1, dtype=torch.int32, device=DEV)
+        many = few[idx].contiguous()
+        plan.step(many, 0.01, 1.0, "explicit", status=status)
+        ok = idx != 5
+        assert torch.equal(many[ok], g[idx][ok]), cells
+        assert torch.equal(status, (~ok).int()), cells
+    plan.set_launch(4, 3)   # a capped grid walks its cells
+    many = torch.tensor(f, device=DEV)[idx].contiguous()
+    assert torch.equal(plan.eval(many), q[idx])
+    plan.close()
