@@ -345,17 +345,21 @@ int launch(const qcoll::KernelArgs& a, hipStream_t stream) {
 // in four). Measured against the split-FP16 matrix kernels (4096 cells, M =
 // 8, hard spheres, float Q): 20 points 195 -> 80 us, 24 points 201 -> 99, 32 points
 // 216 -> 140; 10000 cells of 16 points 103 -> 68 (Maxwell, M = 16: 50.8 -> 37.1);
-// 4000 cells of 48 points 1227 -> 656, of 64 points 1318 -> 920. On 14 and 16 points a
-// plan of fewer than six packed transforms leaves the four transform slots of a
-// wavefront half idle (1000 cells of 16 points, Maxwell, M = 8: 8.0 -> 8.4 us, 2048:
-// 10.0 -> 11.9) and keeps the matrix kernels.
+// 4000 cells of 48 points 1227 -> 656, of 64 points 1318 -> 920. Plans of few
+// packed transforms keep the matrix kernels on the larger grid sizes of each form,
+// where the transform slots of a wavefront are half idle or the code runs too few
+// times to stay ahead of its fetch (steps, matrix and FFT): 16 points, Maxwell, M = 8
+// (four transforms), 2048 cells 10.0 and 11.9 us; 32 points, M = 8, 600 cells 20.0 and
+// 22.2; 32 points, M = 4 (two), 1000 cells 15.9 and 18.5; 64 points, M = 4, 3000 cells
+// 184 and 204.
 // Plans with the projection stay on the matrix kernels: their double Q carries the
 // digits of that arithmetic below 1e-6, and callers compare it with earlier
 // results at double precision. So do the fine grids of Galerkin plans.
 bool fft_supported(const qcoll_plan_s* p) {
+  const int n = p->hp.N;
+  const int few = n == 14 || n == 16 ? 6 : n == 30 || n == 32 ? 5 : n == 26 || n == 28 || n >= 60 ? 3 : 0;
   return p->hp.d == 2 && p->precision == QCOLL_MIX_FX16 && !(p->flags & QCOLL_CONSERVE) && !p->galerkin &&
-         (p->hp.N <= 32 || p->hp.N % 4 == 0) &&
-         !(p->hp.N > 12 && p->hp.N <= 16 && p->hp.packed.size() < 6);
+         (p->hp.N <= 32 || p->hp.N % 4 == 0) && static_cast<int>(p->hp.packed.size()) >= few;
 }
 
 // Filter table of the FFT kernels. Entry q < P is the packed multiplier of gain

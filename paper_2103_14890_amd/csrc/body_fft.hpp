@@ -76,6 +76,12 @@ struct FftGrid {
   static constexpr int kWaveBytes = ((kFh + (XD > V * 64 ? XD : V * 64)) * 8 + 15) / 16 * 16;
 };
 
+template <int NN, int W>
+constexpr int fft_round_bytes() {
+  using F = FftGrid<NN>;
+  return (F::kFh + NN * 64 + 2 + W * F::XD) * 8;
+}
+
 // Transpose within each transform slot: lane r holds line r, register v its
 // point v; afterwards lane c holds point c of every line, register = line.
 template <int NN>
@@ -131,13 +137,19 @@ __device__ __forceinline__ void finish_any(const KernelArgs& a, int64_t cell, co
 // of a workgroup share each cell's transforms: every wavefront computes the
 // spectrum, wavefront wv takes the groups of T transforms wv, wv + 4, ...; the
 // partial sums meet in LDS and wavefront 0 adds them in the order 0, 1, 2, 3.
-template <int NN, bool SINGLE>
+//
+// W > 0, few cells: the W wavefronts of a workgroup take the groups of a cell in turn
+// and add to one gain in LDS, group after group, so the results are bitwise those of
+// one wavefront per cell. lds: the workgroup's fft_round_bytes<NN, W>.
+template <int NN, bool SINGLE, int W = 0>
 __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int64_t stride, bool split, int wv,
                                          double* lds) {
   using F = FftGrid<NN>;
   constexpr int G = F::G, T = F::T, H = F::H, V = F::V;
   double2* fh = reinterpret_cast<double2*>(lds);   // f_hat[k2][k1], k1 = 0 .. N/2
-  double* buf = lds + F::kFh;
+  double* acc = lds + F::kFh;                      // W > 0: the gain, [v][lane], and the group whose turn it is
+  int* turn = reinterpret_cast<int*>(acc + NN * 64);
+  double* buf = W > 0 ? acc + NN * 64 + 2 + wv * F::XD : lds + F::kFh;
   const int g0 = split ? wv : 0, gs = split ? 4 : 1;
   for (int64_t cell = first; cell < a.cells; cell += stride) {
     int lane = threadIdx.x & 63;
@@ -146,32 +158,43 @@ __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int
     const int c = r < NN ? r : 0;
     const float* fc = a.f + cell * static_cast<int64_t>(NN * NN);
     double xr[NN], xi[NN];
-    // ---- forward: along axis 0 (lane = column), transpose, along axis 1 (lane = row k1)
+    auto load_f64 = [&] {
 #pragma unroll
-    for (int v = 0; v < NN; ++v) {
-      xr[v] = static_cast<double>(fc[v * NN + c]);
-      xi[v] = 0.0;
-    }
-    dft<NN, -1>(xr, xi);
-    transpose<NN>(xr, buf, lane);
-    transpose<NN>(xi, buf, lane);
-    dft<NN, -1>(xr, xi);
-    if (lane < H) {
+      for (int v = 0; v < NN; ++v) {
+        xr[v] = static_cast<double>(fc[v * NN + c]);
+        xi[v] = 0.0;
+      }
+    };
+    if constexpr (W == 0) {
+      // ---- forward: along axis 0 (lane = column), transpose, along axis 1 (lane = row k1)
+      load_f64();
+      // Above 16 points the conjugate, by the inverse transform, with zeros that the
+      // compiler does not fold: the form with W > 0 runs these very instructions, rounding
+      // for rounding.
+      constexpr int SG = NN > 16 ? 1 : -1;
+      if constexpr (SG > 0) {
 #pragma unroll
-      for (int v = 0; v < NN; ++v) fh[v * H + lane] = make_double2(xr[v], xi[v]);
+        for (int v = 0; v < NN; ++v) asm volatile("" : "+v"(xi[v]));
+      }
+      dft<NN, SG>(xr, xi);
+      transpose<NN>(xr, buf, lane);
+      transpose<NN>(xi, buf, lane);
+      dft<NN, SG>(xr, xi);
+      if (lane < H) {
+#pragma unroll
+        for (int v = 0; v < NN; ++v) fh[v * H + lane] = make_double2(xr[v], SG > 0 ? -xi[v] : xi[v]);
+      }
+      lds_fence();
     }
-    lds_fence();
 
     double gain[NN];
 #pragma unroll
     for (int v = 0; v < NN; ++v) gain[v] = 0.0;
     const int kap = r < H ? r : (r < NN ? NN - r : 0);                       // the row's partner in 0 .. N/2
     const int neg = (r >= H && r < NN) ? static_cast<int>(0x80000000u) : 0;  // conjugate row
-    // The filter values stream from L2 in batches of four registers, two batches
-    // ahead of their use (the first two of a group before the second pass of the
-    // group before it), the spectrum from LDS one batch ahead. The scheduling
-    // barriers keep the loads of all batches from being issued together, which
-    // would spill the gain.
+    // The filter values of a group come from L2 at once, the spectrum from LDS one
+    // batch of four ahead of its use (the scheduling barriers keep the batches apart:
+    // all loads together would spill the gain).
     constexpr int B = 4, NB = (NN + B - 1) / B;
     double2 m[NB][B];
     auto load_m = [&](int b, int g) {
@@ -184,9 +207,8 @@ __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int
         if (v < NN && v != NN / 2) m[b][j] = *reinterpret_cast<const double2*>(ft + v * H * 16 + off);
       }
     };
-    // both passes of the transforms of group g; the first filter values of group gn
-    // are loaded on the way
-    auto transform = [&](int g, int gn) {
+    // the spectrum times the filters of group g
+    auto filter = [&](int g) {
       double2 z[NB][B];
       auto load_z = [&](int b) {
 #pragma unroll
@@ -217,6 +239,9 @@ __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+    };
+    auto transform = [&](int g) {
+      filter(g);
       dft<NN, 1>(xr, xi);
       transpose<NN>(xr, buf, lane);
       transpose<NN>(xi, buf, lane);
@@ -226,14 +251,62 @@ __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int
     };
     const int full = a.P / T;   // groups of gain transforms only; the group after them ends with the loss
     int g = g0;
+    if constexpr (W > 0) {
+      // The forward transform (its conjugate: the inverse transform of real values) goes
+      // through the loop as well: few cells run each piece of code a few times, and the
+      // instructions fetched for it would take as long as the transform (one cell of 24
+      // points, hard spheres, M = 8: 17.8 us with a forward transform of its own, 14.4 so;
+      // with many wavefronts per SIMD the shared loop is 7 % slower).
+      g = -1;
 #pragma unroll 1
-    for (; g < full; g += gs) {
-      transform(g, g + gs < full ? g + gs : full);
+      for (;;) {
+        if (g < 0) load_f64();
+        else filter(g);
+        const int sign = g < 0 ? 0 : static_cast<int>(0x80000000u);
+        dft<NN, 1>(xr, xi);
+        transpose<NN>(xr, buf, lane);
+        transpose<NN>(xi, buf, lane);
 #pragma unroll
-      for (int v = 0; v < NN; ++v) gain[v] = fma(xr[v], xi[v], gain[v]);
+        for (int v = H; v < NN; ++v) xi[v] = flip(xi[v], sign);
+        dft<NN, 1>(xr, xi);
+        if (g < 0) {
+          if (lane < H && wv == 0) {
+#pragma unroll
+            for (int v = 0; v < NN; ++v) fh[v * H + lane] = make_double2(xr[v], -xi[v]);
+          }
+          if (threadIdx.x == 0) *turn = 0;
+          __syncthreads();
+          g = wv;
+          if (g > full) break;
+          continue;
+        }
+        // The turn of a group is over when its wavefront has added it; the wavefronts of
+        // a workgroup are resident together, so every wait ends.
+        while (__hip_atomic_load(turn, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != g) __builtin_amdgcn_s_sleep(1);
+        if (g > 0) {
+#pragma unroll
+          for (int v = 0; v < NN; ++v) gain[v] = acc[v * 64 + lane];
+        } else {
+#pragma unroll
+          for (int v = 0; v < NN; ++v) gain[v] = 0.0;
+        }
+        if (g == full) break;
+#pragma unroll
+        for (int v = 0; v < NN; ++v) acc[v * 64 + lane] = fma(xr[v], xi[v], gain[v]);
+        __hip_atomic_store(turn, g + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        g += W;
+        if (g > full) break;
+      }
+    } else {
+#pragma unroll 1
+      for (; g < full; g += gs) {
+        transform(g);
+#pragma unroll
+        for (int v = 0; v < NN; ++v) gain[v] = fma(xr[v], xi[v], gain[v]);
+      }
     }
     if (g == full) {   // wavefront-uniform
-      transform(full, full);
+      if constexpr (W == 0) transform(full);
       const int q = full * T + t;
       const bool is_gain = q < a.P, is_loss = q == a.P;   // (neither: an idle slot)
       constexpr int C = 8;
@@ -260,6 +333,15 @@ __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    // The cell's values for the epilogue are on their way while the slots are added.
+    const bool ends = W > 0 ? g == full : !split || wv == 0;
+    float fv[V];
+    if (ends && (a.out_kind == 2 || a.out_kind == 3)) {
+      load_cell<F>(a, cell, lane, fv, static_cast<float>(gain[0]));
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v) fv[v] = 0.0f;
     }
     // ---- add the slots: lane (t, c) keeps rows t V .. t V + V - 1 of column c
     double sum[V];
@@ -297,20 +379,13 @@ __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int
           for (int v = 0; v < V; ++v) sum[v] += part[k * (F::kWaveBytes / 8) + v * 64 + lane];
       }
     }
-    if (!split || wv == 0) {
+    if (ends) {
 #pragma unroll
       for (int v = 0; v < V; ++v)
         if (F::row(v, lane) >= NN || r >= NN) sum[v] = 0.0;
-      float fv[V];
-      if (a.out_kind == 2 || a.out_kind == 3) {
-        load_cell<F>(a, cell, lane, fv, static_cast<float>(sum[0]));
-      } else {
-#pragma unroll
-        for (int v = 0; v < V; ++v) fv[v] = 0.0f;
-      }
       finish_any<F, SINGLE>(a, cell, fv, sum, lane);
     }
-    if (split) __syncthreads();   // the buffers are rewritten by the next cell
+    if (split || W > 0) __syncthreads();   // the buffers are rewritten by the next cell
   }
 }
 

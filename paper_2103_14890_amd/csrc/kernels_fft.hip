@@ -33,6 +33,27 @@ int launch_n(const KernelArgs& args, dim3 grid, dim3 block, hipStream_t stream) 
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
+// A workgroup of four wavefronts per cell.
+template <int N>
+__global__ __launch_bounds__(256, 2) void fft_round_kernel(KernelArgs a) {
+  extern __shared__ double lds[];
+  fft_body<N, true, 4>(a, blockIdx.x, gridDim.x, false, threadIdx.x >> 6, lds);
+}
+
+template <int N>
+int launch_round(const KernelArgs& args, hipStream_t stream) {
+  constexpr int kLds = fft_round_bytes<N, 4>();
+  static_assert(2 * kLds <= 160 * 1024, "two workgroups share a CU's LDS");
+  if (kLds > 64 * 1024) {
+    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(fft_round_kernel<N>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, kLds) == hipSuccess;
+    if (!ok) return -3;
+  }
+  const int64_t blocks = args.cells < args.max_blocks ? args.cells : args.max_blocks;
+  hipLaunchKernelGGL(fft_round_kernel<N>, dim3(static_cast<unsigned>(blocks)), dim3(256), kLds, stream, args);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
 // Cells 0 .. full - 1 four to a wavefront (the first `blocks` workgroups), the rest
 // one to a wavefront.
 template <int N>
@@ -96,6 +117,24 @@ int launch_fft(const KernelArgs& args, hipStream_t stream) {
         case 16: return launch_cells<16>(args, full, stream);
         default: break;
       }
+    }
+  }
+  // Few cells: four wavefronts per cell while one such workgroup per compute unit holds
+  // them all, and two where a cell has enough transforms. 32 points, one cell: hard
+  // spheres, M = 8 (P = 20) 37.8 -> 23.8 us, Maxwell, M = 16 (P = 8) 25 -> 16.6; 300
+  // cells of the latter 28 -> 24.2, but with P = 4 19.3 -> 20.8. (Two wavefronts per
+  // cell beyond that: 700 cells of 32 points, M = 16: 28.6 -> 31.)
+  if (args.n > 16 && args.cells <= static_cast<int64_t>(args.P >= 8 ? 2 : 1) * args.cus) {
+    switch (args.n) {
+      case 18: return launch_round<18>(args, stream);
+      case 20: return launch_round<20>(args, stream);
+      case 22: return launch_round<22>(args, stream);
+      case 24: return launch_round<24>(args, stream);
+      case 26: return launch_round<26>(args, stream);
+      case 28: return launch_round<28>(args, stream);
+      case 30: return launch_round<30>(args, stream);
+      case 32: return launch_round<32>(args, stream);
+      default: break;
     }
   }
   switch (args.n) {

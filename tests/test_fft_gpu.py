@@ -88,3 +88,33 @@ def test_many_cells_equal_few_bitwise(N):
     many = torch.tensor(f, device=DEV)[idx].contiguous()
     assert torch.equal(plan.eval(many), q[idx])
     plan.close()
+
+
+@pytest.mark.parametrize("N", range(18, 33, 2))
+@pytest.mark.parametrize("M", [2, 4, 8])
+def test_few_cells_share_a_workgroup_bitwise(N, M):
+    """With few cells a workgroup of four wavefronts computes a cell (fewer groups of
+    transforms than wavefronts for small M, a last round of one, or several rounds),
+    with many one wavefront: the same digits."""
+    f, L, kernel, _, _ = _case(N, 7)
+    plan = qcoll.Plan(2, N, L, kernel, M)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    limit = 2 * cus
+    src = torch.tensor(f, device=DEV)
+    idx = torch.arange(limit + 1, device=DEV) % 7
+
+    def run(cells, act):
+        t = src[idx[:cells]].contiguous()
+        return act(t)
+
+    def rk(t):
+        plan.step_rk(t, 0.01, 1.0, "bpr343")
+        return t
+
+    for act in (plan.eval, lambda t: plan.step(t, 0.01, 1.0, "imex"), rk):
+        want = run(limit + 1, act)
+        for cells in (1, 5, cus, limit):
+            assert torch.equal(run(cells, act), want[:cells]), cells
+    plan.set_launch(4, 2)   # a capped grid walks its cells
+    assert torch.equal(run(5, plan.eval), run(limit + 1, plan.eval)[:5])
+    plan.close()
