@@ -18,12 +18,14 @@ namespace {
 template <int OUT, bool VEC = false>
 __global__ T64_BOUNDS void fx16_t64_kernel(KernelArgs a) {
   extern __shared__ double2 lds_raw[];
+  stagger_priority();
   t64_body<OUT, true, false, VEC>(a, blockIdx.x, gridDim.x, lds_raw);
 }
 
 template <int OUT, bool VEC = false>
 __global__ T64_BOUNDS void fp32_t64_kernel(KernelArgs a) {
   extern __shared__ double2 lds_raw[];
+  stagger_priority();
   t64_body<OUT, false, false, VEC>(a, blockIdx.x, gridDim.x, lds_raw);
 }
 
