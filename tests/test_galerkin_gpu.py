@@ -117,3 +117,23 @@ def test_galerkin_rejects_other_calls_and_small_work(qc):
     empty = torch.empty((0, 16, 16), dtype=torch.float32, device="cuda")
     assert plan.eval_galerkin(empty).shape == (0, 16, 16)
     plan.close()
+
+
+@pytest.mark.parametrize("N", range(8, 41, 4))
+def test_galerkin_every_tile_count(qc, N):
+    """Every grid size of the device kernels (one to four 16 x 16 tiles per axis, full
+    and ragged), more cells than workgroups, with and without the projection."""
+    L, kernel = 3.0 + 0.16 * N, "maxwell" if N % 8 else "hard_sphere"
+    f = wl.mixture_cells(2, N, L, 3, 700 + N)
+    f = f * np.array([0.5, 1.0, 2.0])[:, None, None]
+    cells = (2048 if N <= 16 else 1024) + 5
+    idx = np.arange(cells) % 3
+    for conserve in (False, True):
+        plan = qc.Plan(2, N, L, kernel, 8, precision="fx16", conserve=conserve, galerkin=True)
+        few = torch.tensor(f, dtype=torch.float32, device="cuda")
+        q = plan.eval_galerkin(few)
+        got, ref = q.cpu().double().numpy(), _ref(f, N, L, kernel, 8, conserve)
+        assert _rel(got, ref) < TOL["fx16"] and _cell_rel(got, ref) < 5 * TOL["fx16"]
+        at = torch.tensor(idx, device="cuda")
+        assert torch.equal(plan.eval_galerkin(few[at].contiguous()), q[at])
+        plan.close()
