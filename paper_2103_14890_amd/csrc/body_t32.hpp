@@ -33,10 +33,11 @@ __device__ __forceinline__ void mma6(const Split3& a, const Split3& b, f32x16& a
 
 // Left operand (K = 64: real part rows, then imaginary part rows) from a
 // complex result tile held as accumulator pairs.
+template <int VV = 16>
 __device__ __forceinline__ void slice_tiles(const f32x16& r0, const f32x16& r1, const f32x16& i0,
                                             const f32x16& i1, float c, Split3 A[4]) {
 #pragma unroll
-  for (int v = 0; v < 16; v += 2) {
+  for (int v = 0; v < VV; v += 2) {
     put2(A[v >> 3], v & 7, split2_acc(r0[v], r1[v], r0[v + 1], r1[v + 1], c));
     put2(A[2 + (v >> 3)], v & 7, split2_acc(i0[v], i1[v], i0[v + 1], i1[v + 1], c));
   }
@@ -46,11 +47,12 @@ __device__ __forceinline__ void slice_tiles(const f32x16& r0, const f32x16& r1, 
 // max (|acc0| + |acc1|) bounds both |acc0| (the part that becomes the lead of
 // the next split) and |acc0 + acc1|. (The sums are canonical floats, so the
 // maxima need no NaN quieting and fold into v_max3.)
+template <int VV = 16>
 __device__ __forceinline__ float tile_absmax(const f32x16& r0, const f32x16& r1, const f32x16& i0,
                                              const f32x16& i1) {
   float m = 0.0f;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
+  for (int v = 0; v < VV; ++v) {
     m = fmaxf(m, fabsf(r0[v]) + fabsf(r1[v]));
     m = fmaxf(m, fabsf(i0[v]) + fabsf(i1[v]));
   }

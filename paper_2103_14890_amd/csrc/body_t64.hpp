@@ -56,6 +56,7 @@ __device__ __forceinline__ Cd cmul(Cd a, Cd b) { return {a.x * b.x - a.y * b.y, 
 // Parity sub-grid x[m1][m2] = f[2 m1 + p1][2 m2 + p2] of one cell in the 32x32
 // result-tile layout, zero outside n' x n'. The lane index is opaque so that the
 // addresses are formed here rather than hoisted out of the cell loop.
+template <int VV>
 __device__ __forceinline__ void load_subgrid(const KernelArgs& a, int64_t cell, int p1, int p2, float* fv) {
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
@@ -63,7 +64,7 @@ __device__ __forceinline__ void load_subgrid(const KernelArgs& a, int64_t cell, 
   const int n = a.n, np = n >> 1;
   const float* fc = a.f + cell * static_cast<int64_t>(n) * n;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
+  for (int v = 0; v < VV; ++v) {
     const int r = rrow(v, h);
     fv[v] = load_or_zero(fc, r < np && c < np, (2 * r + p1) * n + 2 * c + p2);
   }
@@ -78,16 +79,17 @@ struct E32 {
 
 // The FP32 variant's forward (real input, then complex) and inverse (complex,
 // twice) 32-point tile passes, as in the 32x32 FP32 kernel.
+template <int VV>
 __device__ __forceinline__ void fwd_fp32(const E32& E, const float* fv, f32x16& fre, f32x16& fim) {
   f32x16 re{}, im{};
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
+  for (int v = 0; v < VV; ++v) {
     re = mfma32(fv[v], E.r[v], re);
     im = mfma32(fv[v], E.n[v], im);
   }
   fre = fim = f32x16{};
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
+  for (int v = 0; v < VV; ++v) {
     fre = mfma32(re[v], E.r[v], fre);
     fre = mfma32(im[v], E.i[v], fre);
     fim = mfma32(re[v], E.n[v], fim);
@@ -95,11 +97,12 @@ __device__ __forceinline__ void fwd_fp32(const E32& E, const float* fv, f32x16& 
   }
 }
 
+template <int VV>
 __device__ __forceinline__ void inv_fp32(const E32& E, const float* zr, const float* zi, bool want_im, f32x16& yr,
                                          f32x16& yi) {
   f32x16 dr{}, di{};
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
+  for (int v = 0; v < VV; ++v) {
     dr = mfma32(zr[v], E.r[v], dr);
     dr = mfma32(zi[v], E.n[v], dr);
     di = mfma32(zr[v], E.i[v], di);
@@ -107,7 +110,7 @@ __device__ __forceinline__ void inv_fp32(const E32& E, const float* zr, const fl
   }
   yr = yi = f32x16{};
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
+  for (int v = 0; v < VV; ++v) {
     yr = mfma32(dr[v], E.r[v], yr);
     yr = mfma32(di[v], E.n[v], yr);
     if (want_im) {
@@ -134,7 +137,10 @@ __device__ __forceinline__ void inv_fp32(const E32& E, const float* zr, const fl
 // 0, 1, ... and runs the epilogue (first and stride then count work items).
 // VEC: Q is written with 16-byte stores (the caller has checked that the output
 // is 16-byte aligned; n even makes every cell so), else with element stores.
-template <int OUT, bool FX, bool SPLIT = false, bool VEC = false>
+// VV: registers of the 32x32 tiles that hold rows below n' (12 up to n' = 24, n = 48;
+// the rows in the others are zero, and the vector work on them is left out: the same
+// results. 2000 cells of 48 x 48, projection: FX16 675 -> 581 us, FP32 954 -> 815).
+template <int OUT, bool FX, bool SPLIT = false, bool VEC = false, int VV = 16>
 __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int64_t stride, double2* lds_raw) {
   const int kind = OUT < 0 ? a.out_kind : OUT;
   auto can = [](int k) { return OUT == k || (OUT < 0 && k <= 2); };
@@ -171,7 +177,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     (void)eo;
     const float* src = reinterpret_cast<const float*>(a.econst) + lane * 48;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < VV; ++v) {
       E3.r[v] = src[v];
       E3.i[v] = src[16 + v];
       E3.n[v] = src[32 + v];
@@ -185,21 +191,21 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     const int part = SPLIT ? static_cast<int>(item - cell * S) : 0;
     // ---- own parity sub-grid x[m1][m2] = f[2 m1 + p1][2 m2 + p2]
     float fv[16];
-    load_subgrid(a, cell, p1, p2, fv);
+    load_subgrid<VV>(a, cell, p1, p2, fv);
     // ---- n'-point 2D DFT of the sub-grid (as in the N <= 32 kernels); the
     // true values are acc * 2^sc (acc = r0 + r1, i0 + i1)
-    Split3 A[4];
+    Split3 A[4] = {};   // (the rows from register VV on stay zero)
     f32x16 r0{}, r1{}, i0{}, i1{};
     int sc = 0;
     if constexpr (FX) {
       float fm = 0.0f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) fm = fmaxf(fm, fabsf(fv[v]));
+      for (int v = 0; v < VV; ++v) fm = fmaxf(fm, fabsf(fv[v]));
       fm = wave_max(fm);
       const int a0 = 9 - exp_above(fm);
       const double cf = ldexp(1.0, a0);  // FP64: 2^a0 exceeds the FP32 range for max|f| < 2^-118
 #pragma unroll
-      for (int v = 0; v < 16; v += 2)
+      for (int v = 0; v < VV; v += 2)
         put2(A[v >> 3], v & 7, split2_f64(static_cast<double>(fv[v]) * cf, static_cast<double>(fv[v + 1]) * cf));
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
@@ -207,16 +213,16 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
         mma6_lo_lds(A[s], E[kNEi][s], eo + (kNEi * 2 + s) * 64 + lane, i0, i1);
       }
       sc = -(a0 + 9);
-      const int a1 = 9 - exp_above(tile_absmax(r0, r1, i0, i1));
-      slice_tiles(r0, r1, i0, i1, ldexpf(1.0f, a1), A);
+      const int a1 = 9 - exp_above(tile_absmax<VV>(r0, r1, i0, i1));
+      slice_tiles<VV>(r0, r1, i0, i1, ldexpf(1.0f, a1), A);
       pass64_lo_lds(A, E, eo, kEr, kEi, kNEi, kEr, true, r0, r1, i0, i1);
       sc = sc - a1 - 9;
     } else {
-      fwd_fp32(E3, fv, r0, i0);
+      fwd_fp32<VV>(E3, fv, r0, i0);
     }
     // ---- twiddle w^(-k'.p) and exchange: T_p -> f_hat quarter a = w
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < VV; ++v) {
       const Cd t = twv(v);
       const Cd F = {ldexp(static_cast<double>(r0[v]) + static_cast<double>(r1[v]), sc),
                     ldexp(static_cast<double>(i0[v]) + static_cast<double>(i1[v]), sc)};
@@ -230,7 +236,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     // launch 3% shorter).
     double fr[16], fi[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < VV; ++v) {
       double sr = 0.0, si = 0.0;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
@@ -244,11 +250,11 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     }
     __syncthreads();
 #pragma unroll
-    for (int v = 0; v < 16; ++v) zs[(w * 16 + v) * 64 + lane] = {fr[v], fi[v]};
+    for (int v = 0; v < VV; ++v) zs[(w * 16 + v) * 64 + lane] = {fr[v], fi[v]};
 
     double gain[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) gain[v] = 0.0;
+    for (int v = 0; v < VV; ++v) gain[v] = 0.0;
     int sd_last = 0;
     // one transform: q < P a gain transform (Re * Im of its inverse DFT), q = P
     // the loss multiplier (real part only); the loss transform is issued after
@@ -276,10 +282,10 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       float zmh = 0.0f;
       Cd fq[16];   // f_hat_a, from this wave's slot, which then takes Z_a
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         if (v == kMv) {
 #pragma unroll
-          for (int u = kMv; u < 16; ++u) mvv[u] = mq[u * 64 + ml];
+          for (int u = kMv; u < VV; ++u) mvv[u] = mq[u * 64 + ml];
           __builtin_amdgcn_sched_barrier(0);
         }
         fq[v] = zs[(w * 16 + v) * 64 + lane];
@@ -308,7 +314,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       const Cd c2b = FX ? Cd{ldexp(c2.x, b), ldexp(c2.y, b)} : c2;
       float zr[16], zi[16];
 #pragma unroll
-      for (int v = 0; v < 16; v += 2) {
+      for (int v = 0; v < VV; v += 2) {
         double gr[2], gi[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -337,18 +343,18 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       __syncthreads();
       // every wave has read the Z slots: f_hat_a back into this wave's slot
 #pragma unroll
-      for (int v = 0; v < 16; ++v) zs[(w * 16 + v) * 64 + lane] = fq[v];
+      for (int v = 0; v < VV; ++v) zs[(w * 16 + v) * 64 + lane] = fq[v];
       if constexpr (FX) {
         pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, true, r0, r1, i0, i1);
         int sd = a.filt_exp[q] - b - 9;   // Z_a carried the filter mantissas
-        const int a2 = 9 - exp_above(tile_absmax(r0, r1, i0, i1));
-        slice_tiles(r0, r1, i0, i1, ldexpf(1.0f, a2), A);
+        const int a2 = 9 - exp_above(tile_absmax<VV>(r0, r1, i0, i1));
+        slice_tiles<VV>(r0, r1, i0, i1, ldexpf(1.0f, a2), A);
         pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, G, r0, r1, i0, i1);  // loss: real part only
         sd = sd - a2 - 9;
         if constexpr (G) {
           const double wq = ldexp(1.0, 2 * sd);
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
+          for (int v = 0; v < VV; ++v) {
             double re = static_cast<double>(r0[v]) + static_cast<double>(r1[v]);
             double im = static_cast<double>(i0[v]) + static_cast<double>(i1[v]);
             gain[v] = fma(re * wq, im, gain[v]);
@@ -357,10 +363,10 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
           sd_last = sd;
         }
       } else {
-        inv_fp32(E3, zr, zi, G, r0, i0);   // loss: real part only
+        inv_fp32<VV>(E3, zr, zi, G, r0, i0);   // loss: real part only
         if constexpr (G) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) gain[v] += static_cast<double>(r0[v] * i0[v]);
+          for (int v = 0; v < VV; ++v) gain[v] += static_cast<double>(r0[v] * i0[v]);
         }
       }
     };
@@ -371,7 +377,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     const bool own_loss = !SPLIT || part == a.P % S;   // workgroup-uniform
     auto loss_term = [&]() {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const double lf = FX ? ldexp(static_cast<double>(r0[v]) + static_cast<double>(r1[v]), sd_last)
                              : static_cast<double>(r0[v]);
         gain[v] -= static_cast<double>(fv[v]) * lf;
@@ -379,21 +385,21 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     };
     if constexpr (!SPLIT) {
       transform(a.P, std::false_type{});
-      load_subgrid(a, cell, p1, p2, fv);   // not held in registers through the forward transform
+      load_subgrid<VV>(a, cell, p1, p2, fv);   // not held in registers through the forward transform
       loss_term();
     }
     for (int q = part; q < a.P; q += S) transform(q, std::true_type{});
     if constexpr (SPLIT) {
       if (own_loss) transform(a.P, std::false_type{});
-      load_subgrid(a, cell, p1, p2, fv);
+      load_subgrid<VV>(a, cell, p1, p2, fv);
       if (own_loss) loss_term();
     } else if ((can(2) && kind == 2) || (can(3) && kind == 3)) {
-      load_subgrid(a, cell, p1, p2, fv);   // the updates read f again (not held through the transforms)
+      load_subgrid<VV>(a, cell, p1, p2, fv);   // the updates read f again (not held through the transforms)
     }
     if constexpr (SPLIT) {
       double* mine = a.split_ws + ((cell * S + part) * 4 + w) * 1024;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) mine[v * 64 + lane] = gain[v];
+      for (int v = 0; v < VV; ++v) mine[v * 64 + lane] = gain[v];
       __threadfence();   // the part is visible device-wide before it is counted
       __syncthreads();
       if (threadIdx.x == 0) red[20] = atomicAdd(&a.split_cnt[cell], 1) == S - 1 ? 1.0 : 0.0;
@@ -403,11 +409,11 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       if (!last) continue;
       __threadfence();   // the other parts' results are read after their counts
 #pragma unroll
-      for (int v = 0; v < 16; ++v) gain[v] = 0.0;
+      for (int v = 0; v < VV; ++v) gain[v] = 0.0;
       for (int j = 0; j < S; ++j) {
         const double* pj = a.split_ws + ((cell * S + j) * 4 + w) * 1024;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) gain[v] += pj[v * 64 + lane];
+        for (int v = 0; v < VV; ++v) gain[v] += pj[v * 64 + lane];
       }
       if (threadIdx.x == 0) a.split_cnt[cell] = 0;   // zero for the next launch
     }
@@ -430,7 +436,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       T* st = reinterpret_cast<T*>(zs);
       __syncthreads();   // every wave has written its slot back
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const int r = rrow(v, h);
         if (r < np && c < np) st[(2 * r + p1) * n + 2 * c + p2] = value(v);
       }
@@ -456,7 +462,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     } else if (can(1) && kind == 1) {
       double m[4] = {0, 0, 0, 0};
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const double v1 = -a.L + a.dv * (2 * rrow(v, h) + p1);
         m[0] += gain[v];
         m[1] += v1 * gain[v];
@@ -502,7 +508,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       // registers through the stage sums
       double sm[4] = {0, 0, 0, 0};
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const int r = rrow(v, h);
         const double v1 = -a.L + a.dv * (2 * r + p1);
         const double fnv = (r < np && c < np) ? static_cast<double>(fnp[(2 * r + p1) * n + 2 * c + p2]) : 0.0;
@@ -533,7 +539,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       const double e1 = exp_nonpos(-(vr - u1) * (vr - u1) / (2.0 * Tm), ec);
       int bad = 0;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const int r = rrow(v, h);
         const double M = cM * __shfl(e1, r) * e2;   // (every lane takes part in the exchange)
         if (!(r < np && c < np)) continue;
@@ -575,7 +581,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
     } else {
       double rho = 0.0;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) rho += static_cast<double>(fv[v]);
+      for (int v = 0; v < VV; ++v) rho += static_cast<double>(fv[v]);
       rho = wave_sum(rho);
       if (lane == 0) red[w * 4] = rho;
       __syncthreads();
@@ -585,7 +591,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       float* fcell = const_cast<float*>(a.f) + cell * static_cast<int64_t>(n) * n;
       int bad = 0;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const int r = rrow(v, h);
         const float nv = static_cast<float>(static_cast<double>(fv[v]) + k * gain[v]);
         if (r < np && c < np) {

@@ -15,18 +15,18 @@ namespace {
 // work of the other.
 #define T64_BOUNDS __launch_bounds__(256, 2)
 // VEC: 16-byte stores of Q (output kinds 0, 1 and 4 into a 16-byte aligned Q)
-template <int OUT, bool VEC = false>
+template <int OUT, bool VEC, int VV>
 __global__ T64_BOUNDS void fx16_t64_kernel(KernelArgs a) {
   extern __shared__ double2 lds_raw[];
   stagger_priority();
-  t64_body<OUT, true, false, VEC>(a, blockIdx.x, gridDim.x, lds_raw);
+  t64_body<OUT, true, false, VEC, VV>(a, blockIdx.x, gridDim.x, lds_raw);
 }
 
-template <int OUT, bool VEC = false>
+template <int OUT, bool VEC, int VV>
 __global__ T64_BOUNDS void fp32_t64_kernel(KernelArgs a) {
   extern __shared__ double2 lds_raw[];
   stagger_priority();
-  t64_body<OUT, false, false, VEC>(a, blockIdx.x, gridDim.x, lds_raw);
+  t64_body<OUT, false, false, VEC, VV>(a, blockIdx.x, gridDim.x, lds_raw);
 }
 
 }  // namespace
@@ -48,14 +48,21 @@ static bool set_lds_attr() {
   return ok;
 }
 
-template <int OUT, bool VEC>
+// Up to 48 points (n' <= 24) 12 of a tile's 16 registers hold rows.
+template <int VV>
 struct Fx16T64 {
-  static constexpr auto fn = fx16_t64_kernel<OUT, VEC>;
+  template <int OUT, bool VEC>
+  struct K {
+    static constexpr auto fn = fx16_t64_kernel<OUT, VEC, VV>;
+  };
 };
 
-template <int OUT, bool VEC>
+template <int VV>
 struct Fp32T64 {
-  static constexpr auto fn = fp32_t64_kernel<OUT, VEC>;
+  template <int OUT, bool VEC>
+  struct K {
+    static constexpr auto fn = fp32_t64_kernel<OUT, VEC, VV>;
+  };
 };
 
 template <template <int, bool> class K>
@@ -86,11 +93,17 @@ int launch_2d64(const KernelArgs& args, hipStream_t stream) {
   int64_t blocks = args.cells;
   if (blocks > args.max_blocks) blocks = args.max_blocks;
   // 79 KB of dynamic LDS, above the 64 KB default
-  static const bool attr_ok = set_lds_attr<Fx16T64>() && set_lds_attr<Fp32T64>();
+  static const bool attr_ok = set_lds_attr<Fx16T64<12>::K>() && set_lds_attr<Fx16T64<16>::K>() &&
+                              set_lds_attr<Fp32T64<12>::K>() && set_lds_attr<Fp32T64<16>::K>();
   if (!attr_ok) return -3;
   const dim3 grid(static_cast<unsigned>(blocks));
-  if (args.precision == 4) launch_t64<Fx16T64>(args, grid, stream);
-  else launch_t64<Fp32T64>(args, grid, stream);
+  if (args.precision == 4) {
+    if (args.n <= 48) launch_t64<Fx16T64<12>::K>(args, grid, stream);
+    else launch_t64<Fx16T64<16>::K>(args, grid, stream);
+  } else {
+    if (args.n <= 48) launch_t64<Fp32T64<12>::K>(args, grid, stream);
+    else launch_t64<Fp32T64<16>::K>(args, grid, stream);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 

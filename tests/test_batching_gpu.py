@@ -332,3 +332,23 @@ def test_more_plans_than_a_slot_table(qc):
     for p, f, q in zip(plans, fs, qs):
         assert torch.equal(q, p.eval(f))
         p.close()
+
+
+@pytest.mark.parametrize("precision", ["fx16", "fp32"])
+@pytest.mark.parametrize("N", [34, 36, 44, 48, 50])
+def test_64_point_tiles_without_their_empty_rows_bitwise(qc, N, precision):
+    """Up to 48 points the single-plan kernels leave out the tile rows beyond the grid
+    (the batched kernel does not): the same digits."""
+    g = torch.Generator().manual_seed(N)
+    f = torch.rand(5, N, N, generator=g).cuda()
+    plan = qc.Plan(2, N, 8.0, "hard_sphere", 4, precision=precision, conserve=True)
+    q = torch.empty(f.shape, dtype=torch.float64, device="cuda")
+    qc.eval_multi([plan], [f], [q])
+    assert torch.equal(plan.eval(f), q)
+    plan.close()
+    plan = qc.Plan(2, N, 8.0, "maxwell", 2, precision="fp32")
+    a, b = f.clone(), f.clone()
+    plan.step(a, 0.01, 1.0, "imex")
+    qc.step_multi([plan], [b], 0.01, 1.0, "imex")
+    assert torch.equal(a, b)
+    plan.close()
