@@ -153,10 +153,11 @@ __device__ __forceinline__ double2 load_filter_value(const double* filt, int q, 
 // split into the left operand of inverse pass A. The spectrum is re-read from
 // LDS for every transform: an opaque lane offset keeps the compiler from
 // hoisting the reads into 64 live VGPRs.
+template <int VV = 16>
 __device__ __forceinline__ void filtered_split(const double2* mv, const double2* fh, int lane, Split3 A[4]) {
   asm volatile("" : "+v"(lane));
 #pragma unroll
-  for (int v = 0; v < 16; v += 2) {
+  for (int v = 0; v < VV; v += 2) {
     const double2 m0 = mv[v], m1 = mv[v + 1];
     const double2 f0 = fh[v * 64 + lane], f1 = fh[(v + 1) * 64 + lane];
     const double yr0 = m0.x * f0.x - m0.y * f0.y, yi0 = m0.x * f0.y + m0.y * f0.x;
@@ -185,7 +186,12 @@ constexpr int kEoLdsBytes = 2 * kEoHiOffset * 16;
 // w = P mod 4 also the loss), and wavefront 0 sums the four partial results in
 // a fixed order from LDS and runs the epilogue. first and stride then count
 // cells per workgroup; fh is this wavefront's region of four consecutive ones.
-template <int OUT, bool SPLIT = false>  // OUT: 0 eval float, 1 eval double (projection), 2 step, -1 from a.out_kind
+//
+// VV (also in fp32_t32_body): registers of a tile that hold rows of the grid, 12 up to
+// 24 points; the vector work on the zero rows is left out, and in FP32 their matrix
+// instructions (the same results): 4096 cells of 24 x 24 with the projection, FX16
+// 236 -> 216 us, FP32 359 -> 281.
+template <int OUT, bool SPLIT = false, int VV = 16>  // OUT: 0 eval float, 1 eval double (projection), 2 step, -1 from a.out_kind
 __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first, int64_t stride, double2* fh,
                                               const half8* eo) {
   const int lane = threadIdx.x & 63;
@@ -209,7 +215,7 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
 
   for (int64_t cell = first; cell < a.cells; cell += stride) {
     f32x16 r0{}, r1{}, i0{}, i1{};
-    Split3 A[4];
+    Split3 A[4] = {};   // (the rows from register VV on stay zero)
     int s_fh;
     {
       float fv[16];
@@ -218,12 +224,12 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
       // ---- forward pass 1 (real input, contraction over the first axis)
       float fm = 0.0f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) fm = fmaxf(fm, fabsf(fv[v]));
+      for (int v = 0; v < VV; ++v) fm = fmaxf(fm, fabsf(fv[v]));
       fm = wave_max(fm);
       const int a0 = 9 - exp_above(fm);
       const double cf = ldexp(1.0, a0);  // FP64: 2^a0 exceeds the FP32 range for max|f| < 2^-118
 #pragma unroll
-      for (int v = 0; v < 16; v += 2)
+      for (int v = 0; v < VV; v += 2)
         put2(A[v >> 3], v & 7, split2_f64(static_cast<double>(fv[v]) * cf, static_cast<double>(fv[v + 1]) * cf));
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
@@ -235,8 +241,8 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
 
     // ---- forward pass 2 (complex, contraction over the second axis)
     {
-      const int a1 = 9 - exp_above(tile_absmax(r0, r1, i0, i1));
-      slice_tiles(r0, r1, i0, i1, ldexpf(1.0f, a1), A);
+      const int a1 = 9 - exp_above(tile_absmax<VV>(r0, r1, i0, i1));
+      slice_tiles<VV>(r0, r1, i0, i1, ldexpf(1.0f, a1), A);
       pass64_lo_lds(A, E, eo, kEr, kEi, kNEi, kEr, true, r0, r1, i0, i1);
       s_fh -= a1 + 9;
     }
@@ -245,12 +251,12 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
     {
       float fhm = 0.0f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
+      for (int v = 0; v < VV; ++v)
         fhm = fmaxf(fhm, fmaxf(fabsf(r0[v] + r1[v]), fabsf(i0[v] + i1[v])));
       fhm = wave_max(fhm * 1.0000002f);
       const int bsh = 9 - (exp_above(fhm) + 1);
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
+      for (int v = 0; v < VV; ++v)
         fh[v * 64 + lane] = make_double2(ldexp(static_cast<double>(r0[v]) + static_cast<double>(r1[v]), bsh),
                                          ldexp(static_cast<double>(i0[v]) + static_cast<double>(i1[v]), bsh));
       s_fh -= bsh;  // true f_hat = stored value * 2^s_fh
@@ -272,15 +278,15 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
       double2 mv[16];
       const unsigned l16 = opaque_lane16(lane);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) mv[v] = load_filter_value(a.filt, q0, v, l16);
-      filtered_split(mv, fh, lane, A);
+      for (int v = 0; v < VV; ++v) mv[v] = load_filter_value(a.filt, q0, v, l16);
+      filtered_split<VV>(mv, fh, lane, A);
     }
     for (int q = (SPLIT ? wv : 0); q < a.P; q += qs) {
       const int qn = q + qs < a.P ? q + qs : a.P;   // next transform of this wavefront (or the loss entry)
       // inverse pass A (contraction over the first axis)
       pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, true, r0, r1, i0, i1);
-      const int a2 = 9 - exp_above(tile_absmax(r0, r1, i0, i1));
-      slice_tiles(r0, r1, i0, i1, ldexpf(1.0f, a2), A);
+      const int a2 = 9 - exp_above(tile_absmax<VV>(r0, r1, i0, i1));
+      slice_tiles<VV>(r0, r1, i0, i1, ldexpf(1.0f, a2), A);
       // inverse pass B (second axis)
       pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, true, r0, r1, i0, i1);
       const int sd = a.filt_exp[q] + s_fh - 9 - a2 - 9;  // true field = accumulator * 2^sd
@@ -294,29 +300,29 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
       __builtin_amdgcn_sched_barrier(0);
       const double w = ldexp(1.0, 2 * sd);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const double re = static_cast<double>(r0[v]) + static_cast<double>(r1[v]);
         const double im = static_cast<double>(i0[v]) + static_cast<double>(i1[v]);
         gain[v] = fma(re * w, im, gain[v]);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int v = 8; v < 16; ++v) mv[v] = load_filter_value(a.filt, qn, v, l16);
+      for (int v = 8; v < VV; ++v) mv[v] = load_filter_value(a.filt, qn, v, l16);
       __builtin_amdgcn_sched_barrier(0);
-      filtered_split(mv, fh, lane, A);
+      filtered_split<VV>(mv, fh, lane, A);
     }
     float fv[16];
     if (own_loss) {   // wavefront-uniform
       // the loss transform (entry P): only the real part of pass B is needed
       pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, true, r0, r1, i0, i1);
-      const int a2l = 9 - exp_above(tile_absmax(r0, r1, i0, i1));
-      slice_tiles(r0, r1, i0, i1, ldexpf(1.0f, a2l), A);
+      const int a2l = 9 - exp_above(tile_absmax<VV>(r0, r1, i0, i1));
+      slice_tiles<VV>(r0, r1, i0, i1, ldexpf(1.0f, a2l), A);
       pass64_lo_lds(A, E, eo, kEr, kNEi, kEi, kEr, false, r0, r1, i0, i1);
       const int sd_loss = a.filt_exp[a.P] + s_fh - 9 - a2l - 9;
       // the last transform is the loss field: Q = gain - f * loss
       load_cell<Lay32>(a, cell, lane, fv, r0[0]);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         const double lf = ldexp(static_cast<double>(r0[v]) + static_cast<double>(r1[v]), sd_loss);
         gain[v] = gain[v] - static_cast<double>(fv[v]) * lf;
       }
@@ -326,14 +332,14 @@ __device__ __forceinline__ void fx16_t32_body(const KernelArgs& a, int64_t first
       // now); wavefront 0 adds them in the order 0, 1, 2, 3
       double* part = reinterpret_cast<double*>(fh);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) part[v * 64 + lane] = gain[v];
+      for (int v = 0; v < VV; ++v) part[v * 64 + lane] = gain[v];
       __syncthreads();
       if (wv == 0) {
 #pragma unroll
         for (int k = 1; k < 4; ++k) {
           const double* other = reinterpret_cast<const double*>(fh + k * (kFhatLdsBytes / 16));
 #pragma unroll
-          for (int v = 0; v < 16; ++v) gain[v] += other[v * 64 + lane];
+          for (int v = 0; v < VV; ++v) gain[v] += other[v * 64 + lane];
         }
         load_cell<Lay32>(a, cell, lane, fv, static_cast<float>(gain[0]));
         finish_cell<OUT, Lay32>(a, cell, fv, gain, lane);
@@ -638,14 +644,14 @@ __device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-template <int OUT>  // OUT: 0 eval float, 1 eval double (projection), 2 step, -1 from a.out_kind
+template <int OUT, int VV = 16>  // OUT: 0 eval float, 1 eval double (projection), 2 step, -1 from a.out_kind
 __device__ __forceinline__ void fp32_t32_body(const KernelArgs& a, int64_t first, int64_t stride) {
   const int lane = threadIdx.x & 63;
   float Er[16], Ei[16], Ne[16];
   {
     const float* src = reinterpret_cast<const float*>(a.econst) + lane * 48;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < VV; ++v) {
       Er[v] = src[v];
       Ei[v] = src[16 + v];
       Ne[v] = src[32 + v];
@@ -656,13 +662,13 @@ __device__ __forceinline__ void fp32_t32_body(const KernelArgs& a, int64_t first
     load_cell<Lay32>(a, cell, lane, fv);
     f32x16 re{}, im{};
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < VV; ++v) {
       re = mfma32(fv[v], Er[v], re);
       im = mfma32(fv[v], Ne[v], im);
     }
     f32x16 fre{}, fim{};
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = 0; v < VV; ++v) {
       fre = mfma32(re[v], Er[v], fre);
       fre = mfma32(im[v], Ei[v], fre);
       fim = mfma32(re[v], Ne[v], fim);
@@ -680,7 +686,7 @@ __device__ __forceinline__ void fp32_t32_body(const KernelArgs& a, int64_t first
       if constexpr (!loss) {
         const float* mq = a.filt32 + (static_cast<int64_t>(q) * 64 + lane) * 32;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
+        for (int v = 0; v < VV; ++v) {
           float mr = mq[2 * v], mi = mq[2 * v + 1];
           zr[v] = mr * fre[v] - mi * fim[v];
           zi[v] = mr * fim[v] + mi * fre[v];
@@ -688,14 +694,14 @@ __device__ __forceinline__ void fp32_t32_body(const KernelArgs& a, int64_t first
       } else {
         const float* lq = a.loss32 + lane * 16;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
+        for (int v = 0; v < VV; ++v) {
           zr[v] = lq[v] * fre[v];
           zi[v] = lq[v] * fim[v];
         }
       }
       f32x16 dr{}, di{};
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         dr = mfma32(zr[v], Er[v], dr);
         dr = mfma32(zi[v], Ne[v], dr);
         di = mfma32(zr[v], Ei[v], di);
@@ -703,7 +709,7 @@ __device__ __forceinline__ void fp32_t32_body(const KernelArgs& a, int64_t first
       }
       f32x16 yr{}, yi{};
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
+      for (int v = 0; v < VV; ++v) {
         yr = mfma32(dr[v], Er[v], yr);
         yr = mfma32(di[v], Ne[v], yr);
         if constexpr (!loss) {
@@ -713,10 +719,10 @@ __device__ __forceinline__ void fp32_t32_body(const KernelArgs& a, int64_t first
       }
       if constexpr (!loss) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) gain[v] += static_cast<double>(yr[v] * yi[v]);
+        for (int v = 0; v < VV; ++v) gain[v] += static_cast<double>(yr[v] * yi[v]);
       } else {
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
+        for (int v = 0; v < VV; ++v)
           gain[v] = gain[v] - static_cast<double>(fv[v]) * static_cast<double>(yr[v]);
       }
     };

@@ -40,15 +40,16 @@ namespace {
 
 // Two wavefronts per SIMD (at most 256 VGPRs each). Dynamic LDS: the table of
 // DFT-matrix lo parts, then one spectrum per wavefront.
-template <int OUT>
+// VV: as in fx16_t32_body.
+template <int OUT, int VV = 16>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fx16_t32_kernel(KernelArgs a) {
   extern __shared__ double2 lds[];
   half8* eo = reinterpret_cast<half8*>(lds);
   load_eo_table(a, eo);
   const int wpb = blockDim.x >> 6;
   const int w = threadIdx.x >> 6;
-  fx16_t32_body<OUT>(a, static_cast<int64_t>(blockIdx.x) * wpb + w, static_cast<int64_t>(gridDim.x) * wpb,
-                     lds + (kEoLdsBytes + w * kFhatLdsBytes) / 16, eo);
+  fx16_t32_body<OUT, false, VV>(a, static_cast<int64_t>(blockIdx.x) * wpb + w, static_cast<int64_t>(gridDim.x) * wpb,
+                                lds + (kEoLdsBytes + w * kFhatLdsBytes) / 16, eo);
 }
 
 // Few cells: eight wavefronts per cell (fx16_t32_round_body).
@@ -92,11 +93,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void f
                         eo);
 }
 
-template <int OUT>
+template <int OUT, int VV = 16>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fp32_t32_kernel(KernelArgs a) {
   const int wpb = blockDim.x >> 6;
-  fp32_t32_body<OUT>(a, static_cast<int64_t>(blockIdx.x) * wpb + (threadIdx.x >> 6),
-                 static_cast<int64_t>(gridDim.x) * wpb);
+  fp32_t32_body<OUT, VV>(a, static_cast<int64_t>(blockIdx.x) * wpb + (threadIdx.x >> 6),
+                         static_cast<int64_t>(gridDim.x) * wpb);
 }
 
 }  // namespace
@@ -154,14 +155,28 @@ int launch_2d32(const KernelArgs& args, hipStream_t stream) {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
       ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_kernel<4>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
+      ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_kernel<1, 12>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
+      ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_kernel<4, 12>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
       return ok;
     }();
     if (!attr_ok) return -3;
-    if (args.out_kind == 0) hipLaunchKernelGGL(fx16_t32_kernel<0>, grid, block, lds, stream, args);
+    // (the float outputs of such grids run on the FFT kernels)
+    const bool few_rows = args.n <= 24;
+    if (args.out_kind == 1 && few_rows) hipLaunchKernelGGL((fx16_t32_kernel<1, 12>), grid, block, lds, stream, args);
+    else if (args.out_kind == 4 && few_rows) hipLaunchKernelGGL((fx16_t32_kernel<4, 12>), grid, block, lds, stream, args);
+    else if (args.out_kind == 0) hipLaunchKernelGGL(fx16_t32_kernel<0>, grid, block, lds, stream, args);
     else if (args.out_kind == 1) hipLaunchKernelGGL(fx16_t32_kernel<1>, grid, block, lds, stream, args);
     else if (args.out_kind == 2) hipLaunchKernelGGL(fx16_t32_kernel<2>, grid, block, lds, stream, args);
     else if (args.out_kind == 3) hipLaunchKernelGGL(fx16_t32_kernel<3>, grid, block, lds, stream, args);
     else hipLaunchKernelGGL(fx16_t32_kernel<4>, grid, block, lds, stream, args);
+  } else if (args.n <= 24) {
+    if (args.out_kind == 0) hipLaunchKernelGGL((fp32_t32_kernel<0, 12>), grid, block, 0, stream, args);
+    else if (args.out_kind == 1) hipLaunchKernelGGL((fp32_t32_kernel<1, 12>), grid, block, 0, stream, args);
+    else if (args.out_kind == 2) hipLaunchKernelGGL((fp32_t32_kernel<2, 12>), grid, block, 0, stream, args);
+    else if (args.out_kind == 3) hipLaunchKernelGGL((fp32_t32_kernel<3, 12>), grid, block, 0, stream, args);
+    else hipLaunchKernelGGL((fp32_t32_kernel<4, 12>), grid, block, 0, stream, args);
   } else {
     if (args.out_kind == 0) hipLaunchKernelGGL(fp32_t32_kernel<0>, grid, block, 0, stream, args);
     else if (args.out_kind == 1) hipLaunchKernelGGL(fp32_t32_kernel<1>, grid, block, 0, stream, args);

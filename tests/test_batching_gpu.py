@@ -352,3 +352,24 @@ def test_64_point_tiles_without_their_empty_rows_bitwise(qc, N, precision):
     qc.step_multi([plan], [b], 0.01, 1.0, "imex")
     assert torch.equal(a, b)
     plan.close()
+
+
+@pytest.mark.parametrize("precision", ["fx16", "fp32"])
+@pytest.mark.parametrize("N", [18, 20, 22, 24, 26])
+def test_32_point_tiles_without_their_empty_rows_bitwise(qc, N, precision):
+    """The same on the 32x32 tiles (up to 24 points; more cells than compute units, as
+    fewer run on another kernel)."""
+    g = torch.Generator().manual_seed(N)
+    f = torch.rand(300, N, N, generator=g).cuda()
+    plan = qc.Plan(2, N, 8.0, "hard_sphere", 4, precision=precision, conserve=True)
+    q = torch.empty(f.shape, dtype=torch.float64, device="cuda")
+    qc.eval_multi([plan], [f], [q])
+    assert torch.equal(plan.eval(f), q)
+    plan.close()
+    if precision == "fp32":
+        plan = qc.Plan(2, N, 8.0, "maxwell", 2, precision=precision)
+        a, b = f.clone(), f.clone()
+        plan.step(a, 0.01, 1.0, "imex")
+        qc.step_multi([plan], [b], 0.01, 1.0, "imex")
+        assert torch.equal(a, b)
+        plan.close()
