@@ -365,3 +365,24 @@ def test_workspace_calls_run_concurrently_on_one_plan(qc, precision):
     assert torch.equal(p2.eval_ws(f2, small), p2.eval(f2))
     for p in (plan, step_plan, p2):
         p.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fx16"])
+@pytest.mark.parametrize("N", [6, 12, 18, 20, 24, 28, 30])
+def test_padded_planes_hold_nothing_of_another_cell(qc, N, precision):
+    """The passes leave out the planes beyond the grid: a cell's result is bitwise the
+    same after cells of NaN, of its own and of a larger grid, in the same scratch."""
+    T, cells = 16 if N <= 16 else 32, 8
+    f = torch.tensor(wl.mixture_cells(3, N, 8.0, cells, 60 + N), dtype=torch.float32, device="cuda")
+    clean, dirty, full = (qc.Plan(3, n, 8.0, "hard_sphere", 2, precision=precision, conserve=True) for n in (N, N, T))
+    want = clean.eval(f)
+    assert torch.isfinite(want).all()
+    many = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    nan = torch.full((many if T == 16 else many // 2 + 8, N, N, N), float("nan"), device="cuda")
+    assert torch.equal(dirty.eval(torch.cat([nan, f]))[-cells:], want)
+    other = torch.full((many if T == 16 else many // 2 + 8, T, T, T), float("nan"), device="cuda")
+    q0, q1 = torch.empty(other.shape, dtype=torch.float64, device="cuda"), torch.empty_like(want)
+    qc.eval_multi([full, dirty], [other, f], [q0, q1])
+    assert torch.equal(q1, want)
+    for p in (clean, dirty, full):
+        p.close()
