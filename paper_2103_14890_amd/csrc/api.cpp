@@ -1060,7 +1060,7 @@ int qcoll_step_rk(qcoll_plan_t p, float* f, int64_t cells, double dt, double eps
     a.f = l == 2 ? f : work + static_cast<int64_t>(l - 3) * stride;  // stage input F_{l-1}
     a.cells = cells;
     a.dt_eps = dt / eps;
-    a.out_kind = 3;
+    a.out_kind = scheme == QCOLL_IMEX_BPR343 && l == 4 ? 5 : 3;
     a.rk_fn = f;
     a.rk_work = work;
     a.rk_mom = mom;

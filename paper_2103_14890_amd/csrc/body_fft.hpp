@@ -120,7 +120,7 @@ __device__ __forceinline__ void transpose(double (&x)[NN], double* buf, int lane
 }
 
 // The epilogue of an output kind chosen at run time; RK and Galerkin stages (kinds
-// 3 and 4) are single-plan launches only.
+// 3 to 5) are single-plan launches only.
 template <class LY, bool SINGLE>
 __device__ __forceinline__ void finish_any(const KernelArgs& a, int64_t cell, const float* fv, double* q, int lane) {
   if (a.out_kind == 0) finish_cell<0, LY>(a, cell, fv, q, lane);
@@ -128,6 +128,7 @@ __device__ __forceinline__ void finish_any(const KernelArgs& a, int64_t cell, co
   else if (!SINGLE || a.out_kind == 2) finish_cell<2, LY>(a, cell, fv, q, lane);
   else if constexpr (SINGLE) {
     if (a.out_kind == 3) finish_cell<3, LY>(a, cell, fv, q, lane);
+    else if (a.out_kind == 5) finish_cell<5, LY>(a, cell, fv, q, lane);
     else finish_cell<4, LY>(a, cell, fv, q, lane);
   }
 }
@@ -337,7 +338,7 @@ __device__ __forceinline__ void fft_body(const KernelArgs& a, int64_t first, int
     // The cell's values for the epilogue are on their way while the slots are added.
     const bool ends = W > 0 ? g == full : !split || wv == 0;
     float fv[V];
-    if (ends && (a.out_kind == 2 || a.out_kind == 3)) {
+    if (ends && (a.out_kind == 2 || a.out_kind == 3 || a.out_kind == 5)) {
       load_cell<F>(a, cell, lane, fv, static_cast<float>(gain[0]));
     } else {
 #pragma unroll

@@ -58,7 +58,7 @@ __device__ __forceinline__ void block_sum4(double* x, double* red) {
 // Grid sizes 4 R with a body.
 #define QCOLL_FFT64_SIZES(X) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
-// Epilogue: RK and Galerkin stages (kinds 3 and 4) are single-plan launches only
+// Epilogue: RK and Galerkin stages (kinds 3 to 5) are single-plan launches only
 // (SINGLE). Thread (w, lane) holds rows w + 4 b of column `lane`. Whole rows are
 // stored at a time; results and stage slots are streamed past the L2 (non-temporal),
 // so that they do not evict the filters that all cells share.
@@ -122,12 +122,12 @@ __device__ __forceinline__ void finish_rows(const KernelArgs& a, int64_t cell, d
   }
   int bad = 0;
   bool last = true;
-  if (SINGLE && kind == 3) {
+  if (SINGLE && (kind == 3 || kind == 5)) {
     // stage l of the penalised IMEX RK step (finish_cell<3>); fv holds F_{l-1}, q its Q
     int sch = a.rk_scheme - 1, l = a.rk_stage;
     asm volatile("" : "+s"(sch), "+s"(l));   // the tableau is read here, per cell
     const int St = sch == 0 ? 3 : 5;
-    const bool both = sch == 1 && l == 4;   // the last two stages of BPR(3,4,3)
+    const bool both = kind == 5;   // the last two stages of BPR(3,4,3)
     last = l == St || both;
     const double* At5 = kRkAt[1][4];
     const double* Dd5 = kRkD[1][4];

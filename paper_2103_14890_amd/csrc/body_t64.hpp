@@ -125,9 +125,10 @@ __device__ __forceinline__ void inv_fp32(const E32& E, const float* zr, const fl
 // Everything between the passes (quarter exchange, twiddles, filter products,
 // gain) is FP64 in both; the FP32 variant rounds each pass's input to FP32.
 // OUT: 0 eval float, 1 eval double (projection), 2 step, 3 IMEX RK stage, 4
-// double without projection; -1 chosen at run time from a.out_kind among 0..2
-// (the batched launches). Cells first, first + stride, ...; lds_raw is the
-// workgroup's kT64LdsBytes of dynamic LDS (16-byte aligned).
+// double without projection, 5 the last two stages of BPR(3,4,3); -1 chosen at
+// run time from a.out_kind among 0..2 (the batched launches). Cells first, first +
+// stride, ...; lds_raw is the workgroup's kT64LdsBytes of dynamic LDS (16-byte
+// aligned).
 //
 // SPLIT (the latency form of batched launches): a.split workgroups share each
 // cell: work item i is part i % a.split of cell i / a.split; every part computes
@@ -143,6 +144,7 @@ __device__ __forceinline__ void inv_fp32(const E32& E, const float* zr, const fl
 template <int OUT, bool FX, bool SPLIT = false, bool VEC = false, int VV = 16>
 __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int64_t stride, double2* lds_raw) {
   const int kind = OUT < 0 ? a.out_kind : OUT;
+  constexpr bool kRk = OUT == 3 || OUT == 5;
   auto can = [](int k) { return OUT == k || (OUT < 0 && k <= 2); };
   double* lds = reinterpret_cast<double*>(lds_raw);
   Cd* zs = reinterpret_cast<Cd*>(lds);                 // [4][16][64]
@@ -393,7 +395,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       if (own_loss) transform(a.P, std::false_type{});
       load_subgrid<VV>(a, cell, p1, p2, fv);
       if (own_loss) loss_term();
-    } else if ((can(2) && kind == 2) || (can(3) && kind == 3)) {
+    } else if ((can(2) && kind == 2) || kRk) {
       load_subgrid<VV>(a, cell, p1, p2, fv);   // the updates read f again (not held through the transforms)
     }
     if constexpr (SPLIT) {
@@ -487,7 +489,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
         const double v1 = -a.L + a.dv * (2 * rrow(v, h) + p1);
         return gain[v] - (lam[0] + lam[1] * v1 + lam[2] * v2c + lam[3] * (v1 * v1 + v2c * v2c));
       });
-    } else if (can(3) && kind == 3) {
+    } else if (kRk) {
       // stage l of the penalised IMEX RK step (as finish_cell<3> of the 32x32
       // kernels); fv holds the input F_{l-1}, gain its Q (FP64)
       // The scheme and stage indices are made opaque here, so that the tableau
@@ -499,7 +501,7 @@ __device__ __forceinline__ void t64_body(const KernelArgs& a, int64_t first, int
       const int ns = sch == 0 ? 3 : 5;   // stages of the scheme
       const double* At = kRkAt[sch][l - 1];
       const double* Ai = kRkA[sch][l - 1];
-      const bool both = sch == 1 && l == 4;   // the last two stages of BPR(3,4,3)
+      constexpr bool both = OUT == 5;   // the last two stages of BPR(3,4,3)
       const double* At5 = kRkAt[1][4];
       const double* Ai5 = kRkA[1][4];
       const int64_t base = cell * static_cast<int64_t>(n) * n;

@@ -26,14 +26,15 @@ struct KernelArgs {
   int scheme = 0;
   int32_t* status = nullptr;
   int out_kind = 0;             // 0 eval (float Q), 1 eval with projection (double Q), 2 step,
-                                // 3 stage of a multi-stage IMEX step, 4 double Q without projection
-  // out_kind 3: stage rk_stage (2..S) of scheme rk_scheme (1 ARS(2,2,2), 2
+                                // 3 stage of a multi-stage IMEX step, 4 double Q without projection,
+                                // 5 the last two stages (4 and 5) of a BPR(3,4,3) step
+  // out_kind 3 and 5: stage rk_stage (2..S) of scheme rk_scheme (1 ARS(2,2,2), 2
   // BPR(3,4,3)); f holds the stage input F_{l-1}, rk_fn the step's start value
   // f^n (overwritten with the result by the last stage), rk_work the stage
   // slots (F_m, m = 2..S-1, at slot m-2; Q(F_m), m = 1..S-1, at slot S-3+m),
   // rk_stride floats apart. rk_mom: [cells][4] sums over the grid of f^n,
   // v1 f^n, v2 f^n and |v|^2 f^n, written by stage 2 (whose input is f^n) and
-  // read by the later stages (2D grids of at most 32 points per axis).
+  // read by the later stages (2D; the 64-point matrix kernel sums them anew).
   float* rk_fn = nullptr;
   float* rk_work = nullptr;
   double* rk_mom = nullptr;

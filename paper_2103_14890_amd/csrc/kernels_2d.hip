@@ -112,6 +112,7 @@ int launch_2d32(const KernelArgs& args, hipStream_t stream) {
       case 1: return launch_round<1>(args, stream);
       case 2: return launch_round<2>(args, stream);
       case 3: return launch_round<3>(args, stream);
+      case 5: return launch_round<5>(args, stream);
       default: return launch_round<4>(args, stream);
     }
   }
@@ -130,6 +131,8 @@ int launch_2d32(const KernelArgs& args, hipStream_t stream) {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kEoLdsBytes + 8 * kFhatLdsBytes) == hipSuccess;
       ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_pp_kernel<3>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kEoLdsBytes + 8 * kFhatLdsBytes) == hipSuccess;
+      ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_pp_kernel<5>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kEoLdsBytes + 8 * kFhatLdsBytes) == hipSuccess;
       ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_pp_kernel<4>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kEoLdsBytes + 8 * kFhatLdsBytes) == hipSuccess;
       return ok;
@@ -139,6 +142,7 @@ int launch_2d32(const KernelArgs& args, hipStream_t stream) {
     else if (args.out_kind == 1) hipLaunchKernelGGL(fx16_t32_pp_kernel<1>, grid, block, lds, stream, args);
     else if (args.out_kind == 2) hipLaunchKernelGGL(fx16_t32_pp_kernel<2>, grid, block, lds, stream, args);
     else if (args.out_kind == 3) hipLaunchKernelGGL(fx16_t32_pp_kernel<3>, grid, block, lds, stream, args);
+    else if (args.out_kind == 5) hipLaunchKernelGGL(fx16_t32_pp_kernel<5>, grid, block, lds, stream, args);
     else hipLaunchKernelGGL(fx16_t32_pp_kernel<4>, grid, block, lds, stream, args);
   } else if (args.precision == 4) {
     const unsigned lds = kEoLdsBytes + kFhatLdsBytes * wpb;
@@ -152,6 +156,8 @@ int launch_2d32(const KernelArgs& args, hipStream_t stream) {
       ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_kernel<2>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
       ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_kernel<3>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
+      ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_kernel<5>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
       ok &= hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_kernel<4>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, mx) == hipSuccess;
@@ -170,18 +176,21 @@ int launch_2d32(const KernelArgs& args, hipStream_t stream) {
     else if (args.out_kind == 1) hipLaunchKernelGGL(fx16_t32_kernel<1>, grid, block, lds, stream, args);
     else if (args.out_kind == 2) hipLaunchKernelGGL(fx16_t32_kernel<2>, grid, block, lds, stream, args);
     else if (args.out_kind == 3) hipLaunchKernelGGL(fx16_t32_kernel<3>, grid, block, lds, stream, args);
+    else if (args.out_kind == 5) hipLaunchKernelGGL(fx16_t32_kernel<5>, grid, block, lds, stream, args);
     else hipLaunchKernelGGL(fx16_t32_kernel<4>, grid, block, lds, stream, args);
   } else if (args.n <= 24) {
     if (args.out_kind == 0) hipLaunchKernelGGL((fp32_t32_kernel<0, 12>), grid, block, 0, stream, args);
     else if (args.out_kind == 1) hipLaunchKernelGGL((fp32_t32_kernel<1, 12>), grid, block, 0, stream, args);
     else if (args.out_kind == 2) hipLaunchKernelGGL((fp32_t32_kernel<2, 12>), grid, block, 0, stream, args);
     else if (args.out_kind == 3) hipLaunchKernelGGL((fp32_t32_kernel<3, 12>), grid, block, 0, stream, args);
+    else if (args.out_kind == 5) hipLaunchKernelGGL((fp32_t32_kernel<5, 12>), grid, block, 0, stream, args);
     else hipLaunchKernelGGL((fp32_t32_kernel<4, 12>), grid, block, 0, stream, args);
   } else {
     if (args.out_kind == 0) hipLaunchKernelGGL(fp32_t32_kernel<0>, grid, block, 0, stream, args);
     else if (args.out_kind == 1) hipLaunchKernelGGL(fp32_t32_kernel<1>, grid, block, 0, stream, args);
     else if (args.out_kind == 2) hipLaunchKernelGGL(fp32_t32_kernel<2>, grid, block, 0, stream, args);
     else if (args.out_kind == 3) hipLaunchKernelGGL(fp32_t32_kernel<3>, grid, block, 0, stream, args);
+    else if (args.out_kind == 5) hipLaunchKernelGGL(fp32_t32_kernel<5>, grid, block, 0, stream, args);
     else hipLaunchKernelGGL(fp32_t32_kernel<4>, grid, block, 0, stream, args);
   }
   return hipGetLastError() == hipSuccess ? 0 : -3;

@@ -41,6 +41,7 @@ static bool set_lds_attr() {
   set(reinterpret_cast<const void*>(K<1, false>::fn));
   set(reinterpret_cast<const void*>(K<2, false>::fn));
   set(reinterpret_cast<const void*>(K<3, false>::fn));
+  set(reinterpret_cast<const void*>(K<5, false>::fn));
   set(reinterpret_cast<const void*>(K<4, false>::fn));
   set(reinterpret_cast<const void*>(K<0, true>::fn));
   set(reinterpret_cast<const void*>(K<1, true>::fn));
@@ -80,6 +81,7 @@ static void launch_t64(const KernelArgs& args, dim3 grid, hipStream_t stream) {
       break;
     case 2: hipLaunchKernelGGL((K<2, false>::fn), grid, block, kT64LdsBytes, stream, args); break;
     case 3: hipLaunchKernelGGL((K<3, false>::fn), grid, block, kT64LdsBytes, stream, args); break;
+    case 5: hipLaunchKernelGGL((K<5, false>::fn), grid, block, kT64LdsBytes, stream, args); break;
     default:
       if (vec) hipLaunchKernelGGL((K<4, true>::fn), grid, block, kT64LdsBytes, stream, args);
       else hipLaunchKernelGGL((K<4, false>::fn), grid, block, kT64LdsBytes, stream, args);

@@ -222,7 +222,7 @@ __device__ __forceinline__ void finish_cell(const KernelArgs& a, int64_t cell, c
     }
     return;
   }
-  if (OUT == 3) {
+  if (OUT == 3 || OUT == 5) {
     // Stage l of the penalised IMEX RK step (eqs. (GIMEXb), (GIMEX1b), space
     // homogeneous): with M the Maxwellian of the discrete moments of f^n and
     // nu = rho(f^n), S_m = nu (M - F_m), G_m = Q(F_m) - S_m,
@@ -236,7 +236,11 @@ __device__ __forceinline__ void finish_cell(const KernelArgs& a, int64_t cell, c
     const double* At = kRkAt[sch][l - 1];
     const double* Ai = kRkA[sch][l - 1];
     const double* Dd = kRkD[sch][l - 1];
-    const bool both = sch == 1 && l == 4;   // the last two stages of BPR(3,4,3)
+    // The last two stages of BPR(3,4,3), in kernels of their own: in one kernel with
+    // the other stages, which then carried the second update's coefficients and its
+    // reciprocal, a stage took 3-8 % longer (ARS(2,2,2) steps of 4000 cells: FP32 16 x 16
+    // 168 and 154 us, 32 x 32 745 and 718; FX16 32 x 32, Maxwell, M = 8, 150 and 145).
+    constexpr bool both = OUT == 5;
     const double* At5 = kRkAt[1][4];
     const double* Dd5 = kRkD[1][4];
     const double A55 = kRkA[1][4][4];

@@ -406,6 +406,35 @@ def test_step_rk_matches_oracle(qc, scheme, N, precision):
     plan.close()
 
 
+@pytest.mark.parametrize("scheme", ["ars222", "bpr343"])
+@pytest.mark.parametrize("N,precision,cells,tile,waves", [
+    (16, "fx16", 7, 16, 4), (16, "fp32", 7, 16, 4), (16, "fx16", 300, 32, 4), (24, "fx16", 300, 32, 4),
+    (32, "fx16", 7, 32, 4), (32, "fx16", 300, 32, 4), (32, "fx16", 300, 32, 8), (32, "fp32", 7, 32, 4),
+    (24, "fp32", 7, 32, 4), (48, "fx16", 7, 64, 4), (64, "fx16", 7, 64, 4), (64, "fp32", 7, 64, 4)])
+def test_step_rk_on_the_matrix_kernels(qc, scheme, N, precision, cells, tile, waves):
+    """Plans with the projection step on the matrix kernels: every family and launch
+    form of them, and in each the stages one by one (ARS(2,2,2), and stages 2 and 3 of
+    BPR(3,4,3)) and the last two together. The bounds are those of the step test above."""
+    L, dt, eps = 8.0, 0.05, 0.5
+    f0 = wl.mixture_cells(2, N, L, 7, 31 + N)
+    plan = qc.Plan(2, N, L, "hard_sphere", 4, precision=precision, conserve=True)
+    plan.set_tile(tile)
+    plan.set_launch(waves, 1 << 20)
+    at = np.arange(cells) % 7
+    f = torch.tensor(f0[at], dtype=torch.float32, device="cuda")
+    status = torch.full((cells,), -1, dtype=torch.int32, device="cuda")
+    s = sp.Setup(d=2, N=N, L=L, kernel="hard_sphere", M=4)
+    bank = sp.filter_bank(s)
+    want = f0.astype(np.float32).astype(np.float64)
+    for _ in range(2):
+        plan.step_rk(f, dt, eps, scheme, status)
+        want = stepping.imex_rk_penalized(want, lambda F: sp.q_fast(F, s, bank), dt, eps, 2, L, scheme)
+    got = f.cpu().double().numpy()
+    assert np.abs(got - want[at]).max() <= (3e-6 if precision == "fx16" else 3e-5) * np.abs(want).max()
+    assert (status.cpu().numpy() == 0).all()
+    plan.close()
+
+
 def test_step_rk_argument_checks(qc):
     plan = qc.Plan(2, 32, 8.0, "maxwell", 8, precision="fx16")
     f = torch.tensor(wl.mixture_cells(2, 32, 8.0, 4, 1), dtype=torch.float32, device="cuda")
