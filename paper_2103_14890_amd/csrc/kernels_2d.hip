@@ -66,7 +66,8 @@ int launch_round(const KernelArgs& args, hipStream_t stream) {
   static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(fx16_t32_round_kernel<OUT>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, kRoundLdsBytes) == hipSuccess;
   if (!ok) return -3;
-  hipLaunchKernelGGL(fx16_t32_round_kernel<OUT>, dim3(static_cast<unsigned>(args.cells)), dim3(512), kRoundLdsBytes,
+  const int64_t blocks = args.cells < args.max_blocks ? args.cells : args.max_blocks;
+  hipLaunchKernelGGL(fx16_t32_round_kernel<OUT>, dim3(static_cast<unsigned>(blocks)), dim3(512), kRoundLdsBytes,
                      stream, args);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }

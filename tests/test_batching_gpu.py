@@ -3,6 +3,7 @@ different velocity grids), hipGraph capture and replay, and the launch-shape
 autotuner. The operator is cell-local, so every variant must reproduce the
 single-plan results bitwise."""
 
+import ctypes
 import json
 import os
 
@@ -314,6 +315,51 @@ def test_few_cells_equal_the_full_batch_bitwise(qc, N, kernel, M):
     g0 = torch.tensor(wl.mixture_cells(2, 16, 8.0, cells, 61), dtype=torch.float32, device="cuda")
     assert torch.equal(gal.eval_galerkin(g0[3:20].contiguous()), gal.eval_galerkin(g0)[3:20])
     gal.close()
+
+
+class _KernelNode(ctypes.Structure):   # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def _workgroups(qc, call):
+    """Workgroups of each kernel that call(stream) launches, from a captured graph
+    (which is not run)."""
+    lib, s, graph = qc.LIB, torch.cuda.Stream(), ctypes.c_void_p()
+    call(s)
+    s.synchronize()
+    assert lib.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 2) == 0
+    try:
+        call(s)
+    finally:
+        assert lib.hipStreamEndCapture(ctypes.c_void_p(s.cuda_stream), ctypes.byref(graph)) == 0
+    n = ctypes.c_size_t()
+    assert lib.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes, out = (ctypes.c_void_p * n.value)(), []
+    assert lib.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    for node in nodes:
+        p = _KernelNode()
+        assert lib.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append(p.grid[0])
+    assert lib.hipGraphDestroy(graph) == 0
+    return out
+
+
+@pytest.mark.parametrize("cap", [1, 2, 1 << 20])
+def test_few_cells_keep_the_grid_cap(qc, cap):
+    """The launch shape's cap holds for the form that gives a cell eight wavefronts as
+    well: its workgroups then walk several cells, with the same digits."""
+    cells = 5
+    f0 = torch.tensor(wl.mixture_cells(2, 32, 8.0, cells, 92), dtype=torch.float32, device="cuda")
+    plan = qc.Plan(2, 32, 8.0, "hard_sphere", 8, precision="fx16", conserve=True)
+    want = plan.eval(f0)
+    steps = plan.step(f0.clone(), 0.02, 0.5, "imex")
+    plan.set_launch(4, cap)
+    q, g = torch.empty_like(want), f0.clone()
+    assert _workgroups(qc, lambda s: plan.eval(f0, q, stream=s)) == [min(cells, cap)]
+    assert torch.equal(q, want)
+    assert torch.equal(plan.step(g, 0.02, 0.5, "imex"), steps)
+    plan.close()
 
 
 def test_more_plans_than_a_slot_table(qc):
