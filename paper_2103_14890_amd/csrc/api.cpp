@@ -799,7 +799,10 @@ static int plan_create(qcoll_plan_t* out, int d, int n_per_dim, double L, int ke
       rc = build_device_3d(p);
     } else if (fft_supported(p)) {
       p->fft = true;
-      if (p->tile == 16) p->alt_tile = 32;
+      if (p->tile == 16) {
+        p->alt_tile = 32;
+        p->max_blocks = static_cast<int64_t>(cus) * 12;   // two parts share it (launch_cells)
+      }
       rc = build_device_fft(p);
     } else {
       rc = p->tile == 64 ? build_device_2d64(p) : (p->tile == 32 ? build_device_2d32(p) : build_device_2d16(p));

@@ -362,6 +362,28 @@ def test_few_cells_keep_the_grid_cap(qc, cap):
     plan.close()
 
 
+@pytest.mark.parametrize("cap", [1, 2, 3, 100, 1 << 62])
+@pytest.mark.parametrize("N", [4, 10, 16])
+def test_many_small_cells_keep_the_grid_cap(qc, N, cap):
+    """Four cells per wavefront, and the cells left over one per wavefront: both parts
+    together stay within the cap, with the same digits."""
+    cells = 16 * torch.cuda.get_device_properties(0).multi_processor_count + 5
+    f0 = torch.tensor(wl.mixture_cells(2, N, 8.0, 7, 93 + N), dtype=torch.float32, device="cuda")
+    f0 = f0[torch.arange(cells, device="cuda") % 7].contiguous()
+    plan = qc.Plan(2, N, 8.0, "hard_sphere", 8, precision="fx16")
+    want = plan.eval(f0)
+    steps = plan.step(f0.clone(), 0.02, 0.5, "imex")
+    plan.set_launch(4, cap)
+    q, g = torch.empty_like(want), f0.clone()
+    grid, = _workgroups(qc, lambda s: plan.eval(f0, q, stream=s))
+    assert grid <= cap
+    q.zero_()
+    plan.eval(f0, q)
+    assert torch.equal(q, want)
+    assert torch.equal(plan.step(g, 0.02, 0.5, "imex"), steps)
+    plan.close()
+
+
 def test_more_plans_than_a_slot_table(qc):
     """Forty slots: three slot tables (concurrently on side streams: few cells), every
     result bitwise that of the single-plan call, twice in a row without a
