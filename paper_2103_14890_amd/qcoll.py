@@ -418,7 +418,8 @@ def step_multi(plans, fs, dt: float, eps: float = 1.0, scheme: str = "explicit",
     cells = (ctypes.c_int64 * n)(*[f.shape[0] for f in fs])
     st = None
     if statuses is not None:
-        st = vps(*[0 if s is None else _address(s, i32, "status", T) for s in statuses])
+        # (entries beyond the plans are checked and not passed on)
+        st = vps(*[0 if s is None else _address(s, i32, "status", T) for s in statuses][:n])
     _check(LIB.qcoll_step_multi(pl, n, fp, cells, float(dt), float(eps), _SCHEMES[scheme], st,
                                 _stream_ptr(stream)), "qcoll_step_multi")
     return fs

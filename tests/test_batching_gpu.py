@@ -384,6 +384,17 @@ def test_many_small_cells_keep_the_grid_cap(qc, N, cap):
     plan.close()
 
 
+def test_step_multi_takes_a_longer_status_list(qc):
+    """Status entries beyond the plans are ignored (a caller may keep one list for all of
+    its cells' groups and step only some of them)."""
+    plan = qc.Plan(2, 16, 8.0, "maxwell", 8, precision="fx16")
+    f = torch.tensor(wl.mixture_cells(2, 16, 8.0, 3, 94), dtype=torch.float32, device="cuda")
+    st = [torch.full((3,), -1, dtype=torch.int32, device="cuda") for _ in range(3)]
+    qc.step_multi([plan], [f], 0.01, 1.0, "imex", statuses=[st[0], None, st[2]])
+    assert st[0].cpu().tolist() == [0, 0, 0] and st[2].cpu().tolist() == [-1, -1, -1]
+    plan.close()
+
+
 def test_more_plans_than_a_slot_table(qc):
     """Forty slots: three slot tables (concurrently on side streams: few cells), every
     result bitwise that of the single-plan call, twice in a row without a
