@@ -119,17 +119,16 @@ __device__ __forceinline__ void transpose(double (&x)[NN], double* buf, int lane
   }
 }
 
-// The epilogue of an output kind chosen at run time; RK and Galerkin stages (kinds
-// 3 to 5) are single-plan launches only.
+// The epilogue of an output kind chosen at run time: float Q, single-stage update, or
+// (single-plan launches only) RK stage; the plans of these kernels have neither the
+// projection nor a Galerkin grid.
 template <class LY, bool SINGLE>
 __device__ __forceinline__ void finish_any(const KernelArgs& a, int64_t cell, const float* fv, double* q, int lane) {
   if (a.out_kind == 0) finish_cell<0, LY>(a, cell, fv, q, lane);
-  else if (a.out_kind == 1) finish_cell<1, LY>(a, cell, fv, q, lane);
   else if (!SINGLE || a.out_kind == 2) finish_cell<2, LY>(a, cell, fv, q, lane);
   else if constexpr (SINGLE) {
     if (a.out_kind == 3) finish_cell<3, LY>(a, cell, fv, q, lane);
-    else if (a.out_kind == 5) finish_cell<5, LY>(a, cell, fv, q, lane);
-    else finish_cell<4, LY>(a, cell, fv, q, lane);
+    else finish_cell<5, LY>(a, cell, fv, q, lane);
   }
 }
 

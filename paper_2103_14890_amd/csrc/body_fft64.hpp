@@ -58,10 +58,11 @@ __device__ __forceinline__ void block_sum4(double* x, double* red) {
 // Grid sizes 4 R with a body.
 #define QCOLL_FFT64_SIZES(X) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
-// Epilogue: RK and Galerkin stages (kinds 3 to 5) are single-plan launches only
-// (SINGLE). Thread (w, lane) holds rows w + 4 b of column `lane`. Whole rows are
-// stored at a time; results and stage slots are streamed past the L2 (non-temporal),
-// so that they do not evict the filters that all cells share.
+// Epilogue: float Q, single-stage update, or (single-plan launches only, SINGLE) RK
+// stage; the plans of these kernels have neither the projection nor a Galerkin grid.
+// Thread (w, lane) holds rows w + 4 b of column `lane`. Whole rows are stored at a
+// time; results and stage slots are streamed past the L2 (non-temporal), so that they
+// do not evict the filters that all cells share.
 template <int R, bool SINGLE>
 __device__ __forceinline__ void finish_rows(const KernelArgs& a, int64_t cell, double (&q)[R], int w, double* red) {
   constexpr int N = 4 * R;
@@ -79,40 +80,8 @@ __device__ __forceinline__ void finish_rows(const KernelArgs& a, int64_t cell, d
       for (int b = 0; b < R; ++b) __builtin_nontemporal_store(static_cast<float>(q[b]), &Qc[(w + 4 * b) * N + c]);
     return;
   }
-  if (SINGLE && kind == 4) {
-    double* Qc = reinterpret_cast<double*>(a.q) + base;
-    if (in)
-#pragma unroll
-      for (int b = 0; b < R; ++b) __builtin_nontemporal_store(q[b], &Qc[(w + 4 * b) * N + c]);
-    return;
-  }
   const double v2 = -a.L + a.dv * c;
   auto v1 = [&](int b) { return -a.L + a.dv * (w + 4 * b); };
-  if (kind == 1) {   // Q <- Q - lambda . phi, lambda = G^-1 m (FP64 moments)
-    double m[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int b = 0; b < R; ++b) {
-      const double x = in ? q[b] : 0.0;
-      m[0] += x;
-      m[1] += v1(b) * x;
-      m[2] += v2 * x;
-      m[3] += (v1(b) * v1(b) + v2 * v2) * x;
-    }
-    block_sum4<4>(m, red);
-    double lam[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      lam[i] = a.gram_inv[i * 4 + 0] * m[0] + a.gram_inv[i * 4 + 1] * m[1] + a.gram_inv[i * 4 + 2] * m[2] +
-               a.gram_inv[i * 4 + 3] * m[3];
-    double* Qc = reinterpret_cast<double*>(a.q) + base;
-    if (in)
-#pragma unroll
-      for (int b = 0; b < R; ++b)
-        __builtin_nontemporal_store(
-            q[b] - (lam[0] + lam[1] * v1(b) + lam[2] * v2 + lam[3] * (v1(b) * v1(b) + v2 * v2)),
-            &Qc[(w + 4 * b) * N + c]);
-    return;
-  }
   const float* fc = a.f + base;
   float fv[R];
 #pragma unroll
