@@ -118,3 +118,25 @@ def test_few_cells_share_a_workgroup_bitwise(N, M):
     plan.set_launch(4, 2)   # a capped grid walks its cells
     assert torch.equal(run(5, plan.eval), run(limit + 1, plan.eval)[:5])
     plan.close()
+
+
+@pytest.mark.parametrize("N", SIZES)
+def test_batched_calls_equal_single_plan_calls_bitwise(N):
+    """A slot of a batched call gives the digits of the single-plan call, alone and next
+    to a slot of the matrix kernels (its workgroups full and ragged)."""
+    f, L, kernel, M, _ = _case(N, 7)
+    plan, other = qcoll.Plan(2, N, L, kernel, M), qcoll.Plan(2, 32, L, "maxwell", 4, conserve=True)
+    t = torch.tensor(f, device=DEV)
+    g = torch.tensor(wl.mixture_cells(2, 32, L, 3, 90), dtype=torch.float32, device=DEV)
+    want, want_g = plan.eval(t), other.eval(g)
+    stepped, stepped_g = plan.step(t.clone(), 0.01, 1.0, "imex"), other.step(g.clone(), 0.01, 1.0, "imex")
+    for mixed in (False, True):
+        plans, fs = ([plan, other], [t, g]) if mixed else ([plan], [t])
+        qs = [torch.empty_like(want), torch.empty_like(want_g)][:len(plans)]
+        qcoll.eval_multi(plans, fs, qs)
+        assert torch.equal(qs[0], want) and (not mixed or torch.equal(qs[1], want_g))
+        fs = [x.clone() for x in fs]
+        qcoll.step_multi(plans, fs, 0.01, 1.0, "imex")
+        assert torch.equal(fs[0], stepped) and (not mixed or torch.equal(fs[1], stepped_g))
+    plan.close()
+    other.close()
