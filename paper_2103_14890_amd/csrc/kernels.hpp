@@ -54,6 +54,7 @@ struct KernelArgs {
   double* split_ws = nullptr;
   int* split_cnt = nullptr;
   int cus = 256;                // compute units (rules on few and many cells)
+  int stagger = 0;              // 64-point matrix kernels: issue priority for every second wavefront
   int waves_per_block = 4;      // launch shape (1, 2 or 4 wavefronts, one cell each)
   int64_t max_blocks = 1 << 20; // grid cap; waves loop over cells beyond it
 };

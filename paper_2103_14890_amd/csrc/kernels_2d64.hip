@@ -18,14 +18,14 @@ namespace {
 template <int OUT, bool VEC, int VV>
 __global__ T64_BOUNDS void fx16_t64_kernel(KernelArgs a) {
   extern __shared__ double2 lds_raw[];
-  stagger_priority();
+  if (a.stagger) stagger_priority();
   t64_body<OUT, true, false, VEC, VV>(a, blockIdx.x, gridDim.x, lds_raw);
 }
 
 template <int OUT, bool VEC, int VV>
 __global__ T64_BOUNDS void fp32_t64_kernel(KernelArgs a) {
   extern __shared__ double2 lds_raw[];
-  stagger_priority();
+  if (a.stagger) stagger_priority();
   t64_body<OUT, false, false, VEC, VV>(a, blockIdx.x, gridDim.x, lds_raw);
 }
 
@@ -66,6 +66,22 @@ struct Fp32T64 {
   };
 };
 
+// Whether every second wavefront gets issue priority (stagger_priority). Two workgroups
+// share a CU and the favoured one runs ahead: that helps while the last round of cells
+// fills no more than half of the places (the favoured workgroups take it early), and
+// costs where it fills more (the others end late). 64 x 64, Maxwell, M = 8, without and
+// with: 640 and 1152 cells 75.4 -> 71.9, 118.2 -> 113.0 us, but 896 and 1472 cells 94.4 ->
+// 95.8, 141.0 -> 156.7. From four rounds on it helps whole rounds (2048 to 6144 cells, 0 to
+// 3 % less) and does either with others (3 % less to 4 % more, 2112 to 7000 cells), until
+// the last round counts for little: 20000 cells, hard spheres, M = 16, 0.5-1.3 % less. The
+// FP32 kernel gains 1 to 3 % below four rounds, and from there on loses up to 10 % (2048
+// cells of 48 x 48).
+static int stagger_rule(const KernelArgs& a) {
+  const int64_t cus = a.cus, last = a.cells % (2 * cus);
+  if (a.cells < 8 * cus) return last > 0 && last <= cus;
+  return a.precision == 4 && (last == 0 || a.cells >= 32 * cus);
+}
+
 template <template <int, bool> class K>
 static void launch_t64(const KernelArgs& args, dim3 grid, hipStream_t stream) {
   const dim3 block(256);
@@ -99,12 +115,14 @@ int launch_2d64(const KernelArgs& args, hipStream_t stream) {
                               set_lds_attr<Fp32T64<12>::K>() && set_lds_attr<Fp32T64<16>::K>();
   if (!attr_ok) return -3;
   const dim3 grid(static_cast<unsigned>(blocks));
+  KernelArgs a = args;
+  a.stagger = stagger_rule(args);
   if (args.precision == 4) {
-    if (args.n <= 48) launch_t64<Fx16T64<12>::K>(args, grid, stream);
-    else launch_t64<Fx16T64<16>::K>(args, grid, stream);
+    if (args.n <= 48) launch_t64<Fx16T64<12>::K>(a, grid, stream);
+    else launch_t64<Fx16T64<16>::K>(a, grid, stream);
   } else {
-    if (args.n <= 48) launch_t64<Fp32T64<12>::K>(args, grid, stream);
-    else launch_t64<Fp32T64<16>::K>(args, grid, stream);
+    if (args.n <= 48) launch_t64<Fp32T64<12>::K>(a, grid, stream);
+    else launch_t64<Fp32T64<16>::K>(a, grid, stream);
   }
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }

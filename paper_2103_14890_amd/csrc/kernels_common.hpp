@@ -38,8 +38,8 @@ __device__ __forceinline__ float wave_max(float x) {
 
 // Give every second wavefront of a SIMD issue priority over its neighbour, so that one
 // issues matrix instructions while the other is in its vector phase (the 64-point
-// kernel; 4096 cells of 48 x 48 points, FX16: 1220 -> 1200 us. On the 32-point kernel,
-// which the matrix rate bounds, it costs 15 %; in 3D it makes no difference).
+// kernels, with a rule on the number of cells. On the 32-point kernel, which the matrix
+// rate bounds, it costs 15 %; in 3D it makes no difference).
 __device__ __forceinline__ void stagger_priority() {
   if (__builtin_amdgcn_s_getreg((31 << 11) | 4) & 1) __builtin_amdgcn_s_setprio(2);
 }
