@@ -31,3 +31,13 @@ def test_kernels_without_spills(name):
     assert kernels, name
     for k in kernels:
         assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, k[".name"]
+
+
+@pytest.mark.parametrize("name", ["fx16_t16_kernelILi%dEEE", "fp32_t16_kernelILi%dEEE", "fx16_t32_kernelILi%dELi16EEE",
+                                  "fp32_t32_kernelILi%dELi12EEE", "fp32_t32_kernelILi%dELi16EEE"])
+def test_projection_holds_no_table_in_lane_registers(name):
+    """The 16 entries of the inverse Gram matrix (32 registers) stay out of the lanes'
+    registers: the kernel with the projection has about as many as the one without."""
+    regs = {n: k[".vgpr_count"] for n, k in _kernels().items()}
+    plain, proj = (next(v for n, v in regs.items() if name % kind in n) for kind in (0, 1))
+    assert proj <= plain + 12
