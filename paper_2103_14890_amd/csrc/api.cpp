@@ -870,6 +870,7 @@ static int eval_impl(qcoll_plan_t p, const float* f, void* Q, int64_t cells, cha
     c.q = Q;
     c.cells = cells;
     c.N = p->hp.N;
+    c.cus = p->cus;
     c.weights = p->cl_weights;
     c.extra = p->cl_extra;
     c.conserve = (p->flags & QCOLL_CONSERVE) ? 1 : 0;

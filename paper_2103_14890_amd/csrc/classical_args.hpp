@@ -23,6 +23,7 @@ struct ClassicalArgs {
   void* q = nullptr;            // [cells][N][N] float, or double with the projection
   int64_t cells = 0;
   int N = 0;
+  int cus = 256;                // compute units
   const double* weights = nullptr;  // [N][N/2 + 1][N][classical_row(N)]
   const double* extra = nullptr;    // [2][N][N]
   int conserve = 0;

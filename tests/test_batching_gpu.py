@@ -384,6 +384,29 @@ def test_many_small_cells_keep_the_grid_cap(qc, N, cap):
     plan.close()
 
 
+@pytest.mark.parametrize("N", [8, 16, 18, 20, 22, 24])
+def test_classical_workgroup_widths(qc, N):
+    """Four and sixteen (eight) cells per workgroup around the lines of the rule: the same
+    digits, and the widths that the rule names."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    f = torch.tensor(wl.mixture_cells(2, N, 8.0, 7, 95 + N), dtype=torch.float32, device="cuda")
+    plan = qc.Plan(2, N, 8.0, "hard_sphere", 6, classical=True, separable_modes=True, conserve=True)
+    want = plan.eval(f)
+    wide = 8 if N > 20 else 16
+    for cells in (8 * cus, 8 * cus + 3, 16 * cus - 1, 16 * cus, 16 * cus + 3, 24 * cus + 5):
+        at = torch.arange(cells, device="cuda") % 7
+        many = f[at].contiguous()
+        q = torch.empty(many.shape, dtype=torch.float64, device="cuda")
+        grid, = _workgroups(qc, lambda s: plan.eval(many, q, stream=s))
+        rounds = -(-cells // (8 * cus))
+        width = wide if (rounds > 1 if N == 18 else rounds % 2 == 0 if N == 20 else cells >= 16 * cus) else 4
+        assert grid == -(-cells // width), (N, cells)
+        q.zero_()
+        plan.eval(many, q)
+        assert torch.equal(q, want[at]), (N, cells)
+    plan.close()
+
+
 def test_step_multi_takes_a_longer_status_list(qc):
     """Status entries beyond the plans are ignored (a caller may keep one list for all of
     its cells' groups and step only some of them)."""
