@@ -36,14 +36,14 @@ namespace qcoll {
 namespace {
 
 // Workgroups of 16 cells (8 above 20 points: 16 would be two wavefronts on a SIMD, whose
-// registers hold less than a line needs) or, for more workgroups, of 4. Up to 16 points and above 20, wide from a wide workgroup for
-// every CU on (16 x 16: 4096 cells 37 us with 4, 34 with 16; 512 cells 32 and 33). The
-// wide form of 18 and 20 points spills (47 and 94 registers), but its rounds hold 16
-// cells per CU where those of the narrow form, one wavefront per SIMD, hold 8: a wide
-// round takes 1.15 narrow ones at 18 points and 1.8 at 20. So 18 points are wide from the
-// second narrow round on (2000 cells 49 us with 4, 56 with 16; 2500 cells 93 and 57) and
-// 20 points where the number of narrow rounds is even (2500 cells 106 and 89, 4500 cells
-// 158 and 174, 8192 cells 216 and 204).
+// registers hold less than a line needs) or, for more workgroups, of 4. Up to 16 points
+// and above 20, wide from a wide workgroup for every CU on (16 x 16: 4096 cells 37 us with
+// 4, 34 with 16; 512 cells 32 and 33). The wide form of 18 and 20 points spills (47 and 94
+// registers), but its rounds hold 16 cells per CU where those of the narrow form, one
+// wavefront per SIMD, hold 8: a wide round takes 1.15 narrow ones at 18 points and 1.8 at
+// 20. So 18 points are wide from the second narrow round on (2000 cells 49 us with 4, 56
+// with 16; 2500 cells 93 and 57) and 20 points where the number of narrow rounds is even
+// (2500 cells 106 and 89, 4500 cells 158 and 174, 8192 cells 216 and 204).
 static bool classical_wide(const ClassicalArgs& a) {
   const int64_t narrow_rounds = (a.cells + 8 * a.cus - 1) / (8 * a.cus);
   if (a.N == 18) return narrow_rounds > 1;

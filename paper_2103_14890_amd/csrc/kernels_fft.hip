@@ -101,17 +101,20 @@ int launch_fft(const KernelArgs& args, hipStream_t stream) {
   if (blocks > args.max_blocks) blocks = args.max_blocks;
   const dim3 grid(static_cast<unsigned>(blocks)), block(64 * wpb);
   // Four cells per wavefront from whole rounds of one such wavefront per SIMD on. What
-  // is left over joins them where it would take longer a cell per wavefront: a round
-  // costs about as much as unit (P + 2) / 5 cells at 1 + G passes each (G groups of four
-  // of the P + 1 transforms) beside other rounds, and half as much again alone, where
-  // those cells get three wavefronts per SIMD. 16 x 16 Maxwell M = 8 (P = 4): 2048 cells
-  // 11.9 us alone and 13 four to a wavefront, 3500 17.8 and 13.3, 7000 23.9 (2904 of
-  // them alone) and 20.5; hard spheres M = 8 (P = 32): 3500 31 and 35, 6000 44 and 56.
+  // is left over joins them where it would take longer a cell per wavefront: with G + 1
+  // passes for each of its cells (G groups of four of the P + 1 transforms) against P + 2
+  // for a round of `unit` cells, from a ratio of 0.3 on alone and of 0.23 on beside other
+  // rounds (measured on 4 to 16 points and P = 1 to 20; the lines are where neither side
+  // gains). Alone, one and four cells per wavefront: 12 x 12, Maxwell, M = 8 (P = 4), 2048
+  // cells 9.5 and 10.0 us, 3500 cells 14.4 and 10.1; 16 x 16, hard spheres, M = 8 (P =
+  // 20), 3000 cells 26.9 and 34.9, 3500 34.7 and 35.1. Beside a round: the former 7000
+  // cells 18.1 and 14.6, the latter 6000 cells 42.7 and 53.0, 7000 50.5 and 53.3, 12000
+  // 80.7 and 79.4.
   if (args.n <= 16 && (args.out_kind == 0 || args.out_kind == 2)) {
     const int64_t unit = 16 * static_cast<int64_t>(args.cus);
     int64_t full = args.cells / unit * unit;
     const int64_t G = args.P / 4 + 1;
-    if (10 * (args.cells - full) * (1 + G) >= (full > 0 ? 2 : 3) * unit * (args.P + 2)) full = args.cells;
+    if (100 * (args.cells - full) * (1 + G) >= (full > 0 ? 23 : 30) * unit * (args.P + 2)) full = args.cells;
     if (full > 0) {
       switch (args.n) {
         case 4: return launch_cells<4>(args, full, stream);
@@ -126,11 +129,13 @@ int launch_fft(const KernelArgs& args, hipStream_t stream) {
     }
   }
   // Few cells: four wavefronts per cell while one such workgroup per compute unit holds
-  // them all, and two where a cell has enough transforms. 32 points, one cell: hard
-  // spheres, M = 8 (P = 20) 37.8 -> 23.8 us, Maxwell, M = 16 (P = 8) 25 -> 16.6; 300
-  // cells of the latter 28 -> 24.2, but with P = 4 19.3 -> 20.8. (Two wavefronts per
-  // cell beyond that: 700 cells of 32 points, M = 16: 28.6 -> 31.)
-  if (args.n > 16 && args.cells <= static_cast<int64_t>(args.P >= 8 ? 2 : 1) * args.cus) {
+  // them all, and two where a cell has enough transforms for its wavefronts (P >= 4). One
+  // and four wavefronts per cell, one cell: 32 points, hard spheres, M = 8 (P = 20) 37.8
+  // and 23.8 us; 24 points, Maxwell, M = 4 (P = 2) 9.8 and 9.6, 200 cells 13.5 and 10.0. 300
+  // cells: 24 points, P = 20, 39.0 and 23.5; 28 points, P = 4, 20.2 and 17.6, P = 3, 16.5
+  // and 17.3; 20 points, P = 4, 13.8 and 12.4, P = 3, 11.3 and 12.1. (Two wavefronts per
+  // cell beyond that: 700 cells of 32 points, Maxwell, M = 16, 28.6 -> 31.)
+  if (args.n > 16 && args.cells <= static_cast<int64_t>(args.P >= 4 ? 2 : 1) * args.cus) {
     switch (args.n) {
       case 18: return launch_round<18>(args, stream);
       case 20: return launch_round<20>(args, stream);

@@ -418,6 +418,22 @@ def test_step_multi_takes_a_longer_status_list(qc):
     plan.close()
 
 
+@pytest.mark.parametrize("N,M,shared", [(28, 8, True), (20, 8, True), (24, 16, True), (28, 6, False), (20, 4, False)])
+def test_two_cells_per_compute_unit_share_workgroups(qc, N, M, shared):
+    """Between one and two cells per compute unit a cell has a workgroup of its own from
+    four transforms (Maxwell, M = 8) on, with the digits of a wavefront per cell."""
+    cells = torch.cuda.get_device_properties(0).multi_processor_count + 44
+    f = torch.tensor(wl.mixture_cells(2, N, 8.0, 7, 97), dtype=torch.float32, device="cuda")
+    at = torch.arange(2 * cells, device="cuda") % 7
+    plan = qc.Plan(2, N, 8.0, "maxwell", M, precision="fx16")
+    want = plan.eval(f[at].contiguous())[:cells]
+    many = f[at[:cells]].contiguous()
+    q = torch.empty_like(want)
+    assert _workgroups(qc, lambda s: plan.eval(many, q, stream=s)) == [cells if shared else -(-cells // 4)]
+    assert torch.equal(plan.eval(many), want)
+    plan.close()
+
+
 def test_more_plans_than_a_slot_table(qc):
     """Forty slots: three slot tables (concurrently on side streams: few cells), every
     result bitwise that of the single-plan call, twice in a row without a
