@@ -253,7 +253,11 @@ int qcoll_step_multi(const qcoll_plan_t* plans, int nplans, float* const* f, con
  * FX16 device plans with N <= 32 (32x32 tile) also take 8: the ping-pong
  * variant, eight cells per workgroup whose two wavefronts per SIMD alternate
  * between matrix and vector phases; its results are bitwise equal to the
- * other shapes. Other values, and 8 for other plans, return QCOLL_EINVAL. */
+ * other shapes. Other values, and 8 for other plans, return QCOLL_EINVAL.
+ * Some launches choose their own cells per workgroup (the grid cap holds for
+ * them too): FX16 plans with few cells on the 32x32 tile or on FFT grids of
+ * more than 16 points (up to one or two per compute unit), and FFT plans with
+ * many cells on grids of up to 16 points (four cells per wavefront). */
 int qcoll_plan_set_launch(qcoll_plan_t plan, int waves_per_block, int64_t max_blocks);
 int qcoll_plan_get_launch(qcoll_plan_t plan, int* waves_per_block, int64_t* max_blocks);
 
@@ -294,8 +298,9 @@ int qcoll_plan_get_split(qcoll_plan_t plan, int* split);
 /* Autotuner: times every launch shape on the caller's f (device, cells cells)
  * with HIP events, `reps` launches each, and keeps the fastest in the plan:
  * tile family (see qcoll_plan_set_tile) x cells per workgroup (1, 2, 4, and 8
- * where the ping-pong variant exists) x grid cap. 2D fast plans only (3D,
- * Galerkin and classical plans have one launch shape: QCOLL_EUNSUPPORTED).
+ * where the ping-pong variant exists) x grid cap; what the launch of so many
+ * cells ignores keeps the plan's value. 2D fast plans only (3D, Galerkin and
+ * classical plans have one launch shape: QCOLL_EUNSUPPORTED).
  * Synchronises the stream; Q (device, as for qcoll_eval) is overwritten. */
 int qcoll_plan_autotune(qcoll_plan_t plan, const float* f, void* Q, int64_t cells, int reps, hipStream_t stream);
 

@@ -1412,6 +1412,12 @@ int qcoll_plan_get_tile(qcoll_plan_t p, int* tile, int* alternate) {
   return QCOLL_OK;
 }
 
+// The launch ignores waves_per_block.
+static bool own_workgroups(const qcoll::KernelArgs& a) {
+  if (a.tile == 64) return false;
+  return a.fft ? qcoll::own_workgroups_fft(a) : a.tile == 32 && qcoll::own_workgroups_2d32(a);
+}
+
 // Time every launch shape on the caller's data with HIP events and keep the
 // fastest in the plan: tile family (2D plans with N <= 16: 16x16 or zero-padded
 // 32x32 MFMA tiles) x cells per workgroup (1, 2, 4; 8 = the ping-pong variant
@@ -1435,7 +1441,7 @@ int qcoll_plan_autotune(qcoll_plan_t p, const float* f, void* Q, int64_t cells, 
   int64_t best_b = p->max_blocks;
   int rc = QCOLL_OK;
   for (int ti = 0; ti < 2 && rc == QCOLL_OK; ++ti) {
-    if (tiles[ti] == 0) continue;
+    if (tiles[ti] == 0 || (ti > 0 && p->fft)) continue;   // (FFT plans: one kernel for both families)
     if (p->tile != tiles[ti]) swap_tile_tables(p);
     for (int w : wpbs) {
       if (w == 8 && !pingpong_ok(p)) continue;
@@ -1445,6 +1451,8 @@ int qcoll_plan_autotune(qcoll_plan_t p, const float* f, void* Q, int64_t cells, 
         a.q = Q;
         a.cells = cells;
         a.out_kind = (p->flags & QCOLL_CONSERVE) ? 1 : 0;
+        // forms with their own workgroups: one launch for every w, timed for the present one
+        if (w != p->waves_per_block && own_workgroups(a)) continue;
         a.waves_per_block = w;
         a.max_blocks = c >= (1 << 30) ? (int64_t{1} << 40) : c * p->cus * (w >= 4 ? 1 : 4 / w);
         if (launch(a, stream)) { rc = QCOLL_EDEVICE; break; }  // warm-up

@@ -55,7 +55,7 @@ struct KernelArgs {
   int* split_cnt = nullptr;
   int cus = 256;                // compute units (rules on few and many cells)
   int stagger = 0;              // 64-point matrix kernels: issue priority for every second wavefront
-  int waves_per_block = 4;      // launch shape (1, 2 or 4 wavefronts, one cell each)
+  int waves_per_block = 4;      // launch shape (1, 2, 4 or 8 wavefronts, one cell each)
   int64_t max_blocks = 1 << 20; // grid cap; waves loop over cells beyond it
 };
 
@@ -121,6 +121,10 @@ int launch_3d(const Args3& args, hipStream_t stream);
 // Single-plan launches (args.tile selects the 16x16 or 32x32 kernel family).
 int launch_fft(const KernelArgs& args, hipStream_t stream);    // args.fft, up to 32 points
 int launch_fft64(const KernelArgs& args, hipStream_t stream);  // args.fft, 36, 40, .. 64 points
+// Forms of launch_fft and launch_2d32 for few cells (and for many small ones) that
+// choose their own cells per workgroup; the grid cap holds for them as well.
+bool own_workgroups_fft(const KernelArgs& args);
+bool own_workgroups_2d32(const KernelArgs& args);
 int launch_2d16(const KernelArgs& args, hipStream_t stream);
 int launch_2d32(const KernelArgs& args, hipStream_t stream);
 int launch_2d64(const KernelArgs& args, hipStream_t stream);

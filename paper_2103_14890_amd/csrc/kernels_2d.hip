@@ -103,11 +103,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 
 }  // namespace
 
+// up to one cell per CU (256 cells 62 -> 31 us; a second round of workgroups would gain little)
+bool own_workgroups_2d32(const KernelArgs& args) { return args.precision == 4 && args.cells <= args.cus; }
+
 int launch_2d32(const KernelArgs& args, hipStream_t stream) {
   if (args.cells <= 0) return 0;
   const int wpb = args.waves_per_block;
-  // up to one cell per CU (256 cells 62 -> 31 us; a second round of workgroups would gain little)
-  if (args.precision == 4 && args.cells <= args.cus) {
+  if (own_workgroups_2d32(args)) {
     switch (args.out_kind) {
       case 0: return launch_round<0>(args, stream);
       case 1: return launch_round<1>(args, stream);

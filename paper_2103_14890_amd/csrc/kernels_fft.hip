@@ -92,7 +92,37 @@ int launch_cells(const KernelArgs& args, int64_t full, hipStream_t stream) {
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
+// Four cells per wavefront from whole rounds of one such wavefront per SIMD on. What
+// is left over joins them where it would take longer a cell per wavefront: with G + 1
+// passes for each of its cells (G groups of four of the P + 1 transforms) against P + 2
+// for a round of `unit` cells, from a ratio of 0.3 on alone and of 0.23 on beside other
+// rounds (measured on 4 to 16 points and P = 1 to 20; the lines are where neither side
+// gains). Alone, one and four cells per wavefront: 12 x 12, Maxwell, M = 8 (P = 4), 2048
+// cells 9.5 and 10.0 us, 3500 cells 14.4 and 10.1; 16 x 16, hard spheres, M = 8 (P =
+// 20), 3000 cells 26.9 and 34.9, 3500 34.7 and 35.1. Beside a round: the former 7000
+// cells 18.1 and 14.6, the latter 6000 cells 42.7 and 53.0, 7000 50.5 and 53.3, 12000
+// 80.7 and 79.4. Returned: the number of cells that go four to a wavefront.
+int64_t cells_of_four(const KernelArgs& args) {
+  if (args.n > 16 || (args.out_kind != 0 && args.out_kind != 2)) return 0;
+  const int64_t unit = 16 * static_cast<int64_t>(args.cus), G = args.P / 4 + 1;
+  const int64_t full = args.cells / unit * unit, left = args.cells - full;
+  return 100 * left * (1 + G) >= (full > 0 ? 23 : 30) * unit * (args.P + 2) ? args.cells : full;
+}
+
+// Few cells: four wavefronts per cell while one such workgroup per compute unit holds
+// them all, and two where a cell has enough transforms for its wavefronts (P >= 4). One
+// and four wavefronts per cell, one cell: 32 points, hard spheres, M = 8 (P = 20) 37.8
+// and 23.8 us; 24 points, Maxwell, M = 4 (P = 2) 9.8 and 9.6, 200 cells 13.5 and 10.0. 300
+// cells: 24 points, P = 20, 39.0 and 23.5; 28 points, P = 4, 20.2 and 17.6, P = 3, 16.5
+// and 17.3; 20 points, P = 4, 13.8 and 12.4, P = 3, 11.3 and 12.1. (Two wavefronts per
+// cell beyond that: 700 cells of 32 points, Maxwell, M = 16, 28.6 -> 31.)
+bool few_cells(const KernelArgs& args) {
+  return args.n > 16 && args.cells <= static_cast<int64_t>(args.P >= 4 ? 2 : 1) * args.cus;
+}
+
 }  // namespace
+
+bool own_workgroups_fft(const KernelArgs& args) { return cells_of_four(args) > 0 || few_cells(args); }
 
 int launch_fft(const KernelArgs& args, hipStream_t stream) {
   if (args.cells <= 0) return 0;
@@ -100,42 +130,19 @@ int launch_fft(const KernelArgs& args, hipStream_t stream) {
   int64_t blocks = (args.cells + wpb - 1) / wpb;
   if (blocks > args.max_blocks) blocks = args.max_blocks;
   const dim3 grid(static_cast<unsigned>(blocks)), block(64 * wpb);
-  // Four cells per wavefront from whole rounds of one such wavefront per SIMD on. What
-  // is left over joins them where it would take longer a cell per wavefront: with G + 1
-  // passes for each of its cells (G groups of four of the P + 1 transforms) against P + 2
-  // for a round of `unit` cells, from a ratio of 0.3 on alone and of 0.23 on beside other
-  // rounds (measured on 4 to 16 points and P = 1 to 20; the lines are where neither side
-  // gains). Alone, one and four cells per wavefront: 12 x 12, Maxwell, M = 8 (P = 4), 2048
-  // cells 9.5 and 10.0 us, 3500 cells 14.4 and 10.1; 16 x 16, hard spheres, M = 8 (P =
-  // 20), 3000 cells 26.9 and 34.9, 3500 34.7 and 35.1. Beside a round: the former 7000
-  // cells 18.1 and 14.6, the latter 6000 cells 42.7 and 53.0, 7000 50.5 and 53.3, 12000
-  // 80.7 and 79.4.
-  if (args.n <= 16 && (args.out_kind == 0 || args.out_kind == 2)) {
-    const int64_t unit = 16 * static_cast<int64_t>(args.cus);
-    int64_t full = args.cells / unit * unit;
-    const int64_t G = args.P / 4 + 1;
-    if (100 * (args.cells - full) * (1 + G) >= (full > 0 ? 23 : 30) * unit * (args.P + 2)) full = args.cells;
-    if (full > 0) {
-      switch (args.n) {
-        case 4: return launch_cells<4>(args, full, stream);
-        case 6: return launch_cells<6>(args, full, stream);
-        case 8: return launch_cells<8>(args, full, stream);
-        case 10: return launch_cells<10>(args, full, stream);
-        case 12: return launch_cells<12>(args, full, stream);
-        case 14: return launch_cells<14>(args, full, stream);
-        case 16: return launch_cells<16>(args, full, stream);
-        default: break;
-      }
+  if (const int64_t full = cells_of_four(args); full > 0) {
+    switch (args.n) {
+      case 4: return launch_cells<4>(args, full, stream);
+      case 6: return launch_cells<6>(args, full, stream);
+      case 8: return launch_cells<8>(args, full, stream);
+      case 10: return launch_cells<10>(args, full, stream);
+      case 12: return launch_cells<12>(args, full, stream);
+      case 14: return launch_cells<14>(args, full, stream);
+      case 16: return launch_cells<16>(args, full, stream);
+      default: break;
     }
   }
-  // Few cells: four wavefronts per cell while one such workgroup per compute unit holds
-  // them all, and two where a cell has enough transforms for its wavefronts (P >= 4). One
-  // and four wavefronts per cell, one cell: 32 points, hard spheres, M = 8 (P = 20) 37.8
-  // and 23.8 us; 24 points, Maxwell, M = 4 (P = 2) 9.8 and 9.6, 200 cells 13.5 and 10.0. 300
-  // cells: 24 points, P = 20, 39.0 and 23.5; 28 points, P = 4, 20.2 and 17.6, P = 3, 16.5
-  // and 17.3; 20 points, P = 4, 13.8 and 12.4, P = 3, 11.3 and 12.1. (Two wavefronts per
-  // cell beyond that: 700 cells of 32 points, Maxwell, M = 16, 28.6 -> 31.)
-  if (args.n > 16 && args.cells <= static_cast<int64_t>(args.P >= 4 ? 2 : 1) * args.cus) {
+  if (few_cells(args)) {
     switch (args.n) {
       case 18: return launch_round<18>(args, stream);
       case 20: return launch_round<20>(args, stream);

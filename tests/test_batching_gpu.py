@@ -434,6 +434,23 @@ def test_two_cells_per_compute_unit_share_workgroups(qc, N, M, shared):
     plan.close()
 
 
+@pytest.mark.parametrize("N,conserve,cells", [(32, True, 5), (24, False, 5), (16, False, 5000)])
+def test_autotune_keeps_what_the_launch_ignores(qc, N, conserve, cells):
+    """Forms for few cells and for many small ones choose their own cells per workgroup
+    (and FFT plans have one kernel for both tile families): the autotuner keeps the plan's
+    values instead of choosing among equal launches."""
+    f = torch.tensor(wl.mixture_cells(2, N, 8.0, cells, 98), dtype=torch.float32, device="cuda")
+    for waves in (1, 2):
+        plan = qc.Plan(2, N, 8.0, "hard_sphere", 8, precision="fx16", conserve=conserve)
+        plan.set_launch(waves, 64)
+        tile = plan.tile()
+        want = plan.eval(f)
+        best = plan.autotune(f, reps=2)
+        assert best["waves_per_block"] == waves and plan.tile() == tile
+        assert torch.equal(plan.eval(f), want)
+        plan.close()
+
+
 def test_more_plans_than_a_slot_table(qc):
     """Forty slots: three slot tables (concurrently on side streams: few cells), every
     result bitwise that of the single-plan call, twice in a row without a
