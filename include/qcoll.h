@@ -52,10 +52,18 @@ enum { QCOLL_MAXWELL = 0, QCOLL_HARD_SPHERE = 1, QCOLL_VHS = 2 };
  *                  operands: a fixed-point leading part whose products sum
  *                  exactly in the FP32 accumulator, plus an FP16 hi/lo
  *                  remainder (six products, two accumulators); spectra,
- *                  filters and all elementwise work in FP64. 2D plans without
- *                  QCOLL_CONSERVE and QCOLL_GALERKIN on grids of up to 32, or of
- *                  36, 40, .. 64 points per axis compute the DFTs as FFTs in FP64 instead (results
- *                  within the same bounds, the transforms exact to FP64). */
+ *                  filters and all elementwise work in FP64.
+ *                  FFT plans: 2D plans without QCOLL_CONSERVE and QCOLL_GALERKIN
+ *                  on grids of up to 32, or of 36, 40, .. 64 points per axis
+ *                  compute the DFTs as FFTs in FP64 instead (results within the
+ *                  same bounds; the error left is the rounding of Q or f to
+ *                  float). Plans of few transforms keep the GEMMs on some grids,
+ *                  where small batches are faster so: fewer than 7 transforms (as
+ *                  qcoll_plan_info counts them) on 14 and 16 points, 6 on 30 and
+ *                  32, 4 on 26, 28, 60 and 64. Plans with QCOLL_CONSERVE keep them
+ *                  too: the double Q of a projected plan has the error of the
+ *                  splits (about 1e-6 of Q), and its digits below that do not
+ *                  change from one version of the library to the next. */
 enum { QCOLL_FP32 = 1, QCOLL_MIX_FX16 = 4 };
 
 /* Time schemes (section 3.4, homogeneous case): the single-stage updates of
@@ -99,9 +107,10 @@ enum {
  * plans, whose scratch area allows one call in flight at a time (the
  * qcoll_eval_ws / qcoll_step_ws calls take a workspace of the caller's and
  * lift that limit). On error *out
- * is set to NULL. Device plans: d = 2 with N <= 32 (grids below 16 or 32 run
- * zero-padded in a 16x16 or 32x32 tile) and 34 <= N <= 64 (radix-2 split into
- * 32-point tiles, one workgroup per cell), both in either precision; d = 3
+ * is set to NULL. Device plans: d = 2 with N <= 32 (GEMMs: grids below 16 or 32
+ * run zero-padded in a 16x16 or 32x32 tile) and 34 <= N <= 64 (GEMMs: radix-2
+ * split into 32-point tiles, one workgroup per cell), both in either precision,
+ * and on the FFT kernels as listed above; d = 3
  * hard spheres with N <= 32 in either precision (zero-padded
  * 16^3 or 32^3 tiles, one workgroup per cell,
  * a scratch area of 144 T^3 bytes per resident workgroup held by the plan; the
@@ -266,7 +275,9 @@ int qcoll_plan_get_launch(qcoll_plan_t plan, int* waves_per_block, int64_t* max_
  * tables of the 32x32 tile kernels (v_mfma_f32_32x32x16_f16 / 32x32x2f32, the
  * grid zero-padded), so either can run them (same Q_h up to rounding; the
  * parity bounds of the plan's precision hold for both). set_tile selects 16
- * or 32 for such plans and returns QCOLL_EINVAL for any other value (other
+ * or 32 for such plans (FFT plans run the same kernel for both; the value then
+ * sets only which launch shapes and split factors they take) and returns
+ * QCOLL_EINVAL for any other value (other
  * plans have one tile family: 32 for 18..32 points, 64 for 34..64); get_tile
  * reports the selected tile and the alternate one (0: none). Selecting a
  * family whose kernels lack the launch shape 8 resets that shape to 4. */
@@ -276,7 +287,7 @@ int qcoll_plan_get_tile(qcoll_plan_t plan, int* tile, int* alternate);
 /* Transform split (latency form for small batches; the operator of section 3.3
  * is a sum over the plan's transforms, so a cell's transforms can be shared out):
  *   1  default: one wavefront (N <= 32) or one workgroup (N > 32) per cell;
- *   4  FX16 plans on the 32x32 tile: a workgroup of four wavefronts per cell,
+ *   4  FX16 plans on the 32x32 tile (FFT plans too): a workgroup of four wavefronts per cell,
  *      each wavefront taking every fourth transform, the partial sums added in
  *      LDS in a fixed order;
  *   2, 4, 8, 16  tile-64 plans (FX16 or FP32): that many workgroups per cell, the

@@ -345,13 +345,21 @@ int launch(const qcoll::KernelArgs& a, hipStream_t stream) {
 // in four). Measured against the split-FP16 matrix kernels (4096 cells, M =
 // 8, hard spheres, float Q): 20 points 195 -> 80 us, 24 points 201 -> 99, 32 points
 // 216 -> 140; 10000 cells of 16 points 103 -> 68 (Maxwell, M = 16: 50.8 -> 37.1);
-// 4000 cells of 48 points 1227 -> 656, of 64 points 1318 -> 920. Plans of few
-// packed transforms keep the matrix kernels on the larger grid sizes of each form,
-// where the transform slots of a wavefront are half idle or the code runs too few
-// times to stay ahead of its fetch (steps, matrix and FFT): 16 points, Maxwell, M = 8
-// (four transforms), 2048 cells 10.0 and 11.9 us; 32 points, M = 8, 600 cells 20.0 and
-// 22.2; 32 points, M = 4 (two), 1000 cells 15.9 and 18.5; 64 points, M = 4, 3000 cells
-// 184 and 204.
+// 4000 cells of 48 points 1227 -> 656, of 64 points 1318 -> 920.
+// A plan has one set of tables for batches of every size, and with few packed
+// transforms P (the transform slots of a wavefront half idle, the code run too few times
+// to stay ahead of its fetch) the FFT form loses small batches on the larger grids of
+// each form. Such plans keep the matrix kernels, also where large batches would gain.
+// Times of the matrix form over those of the FFT form, steps, Maxwell molecules:
+//   points        P  1000 cells  10000      P  1000  10000
+//   14, 16        4  0.92, 0.87  1.23, 1.20  6  1.10, 1.03  1.38, 1.34
+//   points        P  600 cells   6000       P  600   6000
+//   26, 28        2  0.89, 0.83  1.05, 1.04  3  1.07, 1.00  1.28, 1.28
+//   30, 32        4  0.90, 0.87  1.12, 1.11  5  1.04, 0.99  1.31, 1.29
+//   points        P  600 cells   4000       P  600   4000
+//   60, 64        1  0.93, 0.90  0.91, 0.90  3  1.03, 1.03  1.07, 1.08
+// (P = 2 of the last: 1.00, 0.98 and 0.99, 1.00.) Every other size is above 1 from P = 1
+// on, up to 12 points from 2500 cells on (below, 0.92 to 1: launches of about 7 us).
 // Plans with the projection stay on the matrix kernels: their double Q carries the
 // digits of that arithmetic below 1e-6, and callers compare it with earlier
 // results at double precision. So do the fine grids of Galerkin plans.

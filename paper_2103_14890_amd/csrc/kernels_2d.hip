@@ -171,7 +171,8 @@ int launch_2d32(const KernelArgs& args, hipStream_t stream) {
       return ok;
     }();
     if (!attr_ok) return -3;
-    // (the float outputs of such grids run on the FFT kernels)
+    // (float Q of such grids runs on the FFT kernels, but for plans of few transforms on 14
+    // and 16 points; steps of plans with the projection run here with all 16 registers)
     const bool few_rows = args.n <= 24;
     if (args.out_kind == 1 && few_rows) hipLaunchKernelGGL((fx16_t32_kernel<1, 12>), grid, block, lds, stream, args);
     else if (args.out_kind == 4 && few_rows) hipLaunchKernelGGL((fx16_t32_kernel<4, 12>), grid, block, lds, stream, args);

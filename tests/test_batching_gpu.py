@@ -451,6 +451,19 @@ def test_autotune_keeps_what_the_launch_ignores(qc, N, conserve, cells):
         plan.close()
 
 
+@pytest.mark.parametrize("N", [18, 20, 22, 24, 26])
+def test_steps_of_projected_plans_bitwise(qc, N):
+    """The steps of a plan with the projection (more cells than compute units, as fewer run
+    on another kernel) give the digits of the batched call."""
+    f = torch.rand(300, N, N, generator=torch.Generator().manual_seed(N)).cuda()
+    plan = qc.Plan(2, N, 8.0, "hard_sphere", 4, precision="fx16", conserve=True)
+    a, b = f.clone(), f.clone()
+    plan.step(a, 0.01, 1.0, "imex")
+    qc.step_multi([plan], [b], 0.01, 1.0, "imex")
+    assert torch.equal(a, b)
+    plan.close()
+
+
 def test_more_plans_than_a_slot_table(qc):
     """Forty slots: three slot tables (concurrently on side streams: few cells), every
     result bitwise that of the single-plan call, twice in a row without a
